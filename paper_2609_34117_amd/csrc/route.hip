@@ -1,6 +1,8 @@
 // Router of the MoE layer on gfx950: fp32 logits, masked top-k selection and
 // renormalised gates (Section 3.1, Eq. 2 and the renormalisation after it),
 // and the fused route + dispatch of small (decode-sized) batches.
+#include <algorithm>
+
 #include "dispatch_block.h"
 #include "sw_launch.h"
 
@@ -220,38 +222,89 @@ __device__ __forceinline__ int token_group(const Cols& c, int t, int T) {
   return c.R > 1 ? (int)((long long)t * c.R / T) : 0;
 }
 
-// Order key of token t's logit for expert e: z = sum of the KS partials in
-// slice order, plus the bias; 0 marks an ineligible expert (the one logit
-// whose key is 0, a NaN, is nudged to 1).  All partial loads are issued
-// before the first add.
-__device__ __forceinline__ uint32_t logit_key(const float* __restrict__ part, int KS, int T,
-                                              const Cols& c, int t, int e,
-                                              const float* __restrict__ bias,
-                                              const uint8_t* __restrict__ keep_mask) {
-  if (e >= c.m || (keep_mask != nullptr && keep_mask[e] == 0)) return 0u;
-  const float* p = part + (size_t)t * c.ld + e;
+// The partial logits of one token for this lane's KPL experts, and what the
+// lane knows of those experts whatever the token: their biases and whether
+// they may be selected.  Every load is unconditional, at a clamped index, and
+// nothing is computed between the loads: with a branch around each expert's
+// loads the compiler waits for them one expert at a time, a memory round trip
+// each (three with a mask and a bias): logits and top-k of 64 tokens over 256
+// experts took 9.2 us that way and take 7.7 us this way.
+template <int KPL>
+struct LogitParts {
+  float z[kMaxSplit][KPL];
+  float gate[kMaxSplit];  // of the shared expert's gate column, with one
+};
+
+template <int KPL>
+struct LaneExperts {
+  float bias[KPL];
+  bool ok[KPL];
+};
+
+template <int KPL>
+__device__ __forceinline__ LogitParts<KPL> load_logits(const float* __restrict__ part, int KS,
+                                                       int T, const Cols& c, int t,
+                                                       const int (&eid)[KPL]) {
+  LogitParts<KPL> l;
+  const float* p = part + (size_t)min(t, T - 1) * c.ld;
   const size_t plane = (size_t)T * c.ld;
-  float zp[kMaxSplit];
 #pragma unroll
-  for (int ks = 0; ks < kMaxSplit; ++ks) zp[ks] = ks < KS ? p[ks * plane] : 0.f;
-  float z = zp[0];
+  for (int ks = 0; ks < kMaxSplit; ++ks) {
 #pragma unroll
-  for (int ks = 1; ks < kMaxSplit; ++ks)
-    if (ks < KS) z += zp[ks];
-  if (bias != nullptr) z += bias[e];
-  return max(f32_order_key(z), 1u);
+    for (int q = 0; q < KPL; ++q) l.z[ks][q] = 0.f;
+    if (ks < KS) {  // uniform
+#pragma unroll
+      for (int q = 0; q < KPL; ++q) l.z[ks][q] = p[ks * plane + min(eid[q], c.m - 1)];
+    }
+    l.gate[ks] = ks < KS && c.S > 0 ? p[ks * plane + c.m] : 0.f;  // uniform
+  }
+  return l;
 }
 
-// Gate of the shared expert for token t (Section 3.3): the sigmoid of its
-// gate logit, the partials of column m summed in slice order like every
-// other logit.
-__device__ __forceinline__ float shared_gate(const float* __restrict__ part, int KS, int T,
-                                             const Cols& c, int t) {
-  const float* p = part + (size_t)t * c.ld + c.m;
-  const size_t plane = (size_t)T * c.ld;
-  float zp[kMaxSplit];
+template <int KPL>
+__device__ __forceinline__ LaneExperts<KPL> load_experts(const Cols& c, const int (&eid)[KPL],
+                                                         const float* __restrict__ bias,
+                                                         const uint8_t* __restrict__ keep_mask) {
+  LaneExperts<KPL> x;
+  uint8_t keep[KPL];
 #pragma unroll
-  for (int ks = 0; ks < kMaxSplit; ++ks) zp[ks] = ks < KS ? p[ks * plane] : 0.f;
+  for (int q = 0; q < KPL; ++q) {
+    x.bias[q] = 0.f;
+    keep[q] = 1;
+  }
+  if (bias != nullptr) {
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) x.bias[q] = bias[min(eid[q], c.m - 1)];
+  }
+  if (keep_mask != nullptr) {
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) keep[q] = keep_mask[min(eid[q], c.m - 1)];
+  }
+#pragma unroll
+  for (int q = 0; q < KPL; ++q) x.ok[q] = eid[q] < c.m && keep[q] != 0;
+  return x;
+}
+
+// Order keys of a token's logits: z = sum of the KS partials in slice order,
+// plus the bias; 0 marks an ineligible expert (the one logit whose key is 0,
+// a NaN, is nudged to 1).
+template <int KPL>
+__device__ __forceinline__ void logit_keys(const LogitParts<KPL>& l, const LaneExperts<KPL>& x,
+                                           int KS, bool biased, uint32_t (&key)[KPL]) {
+#pragma unroll
+  for (int q = 0; q < KPL; ++q) {
+    float z = l.z[0][q];
+#pragma unroll
+    for (int ks = 1; ks < kMaxSplit; ++ks)
+      if (ks < KS) z += l.z[ks][q];
+    if (biased) z += x.bias[q];
+    key[q] = x.ok[q] ? max(f32_order_key(z), 1u) : 0u;
+  }
+}
+
+// Gate of the shared expert (Section 3.3): the sigmoid of its gate logit, the
+// partials of column m summed in slice order like every other logit.
+__device__ __forceinline__ float shared_gate(const float (&zp)[kMaxSplit], int KS) {
   float z = zp[0];
 #pragma unroll
   for (int ks = 1; ks < kMaxSplit; ++ks)
@@ -259,19 +312,8 @@ __device__ __forceinline__ float shared_gate(const float* __restrict__ part, int
   return 1.0f / (1.0f + expf(-z));
 }
 
-// Reductions inside one 16-lane row (quad swaps, then the half-row and row
-// mirrors): every lane of the row ends with the row's result.
-template <typename Op>
-__device__ __forceinline__ uint32_t row_reduce_u32(uint32_t v, uint32_t identity, Op op) {
-  v = op(v, dpp_mov<dpp::kXor1>(identity, v));
-  v = op(v, dpp_mov<dpp::kXor2>(identity, v));
-  v = op(v, dpp_mov<dpp::kHalfMirror>(identity, v));
-  v = op(v, dpp_mov<dpp::kMirror>(identity, v));
-  return v;
-}
-
-// Result of one token's selection, held by the lanes of its row or wave:
-// lane j < k holds slot j.
+// Result of one token's selection, held by the lanes of its wave: lane j < k
+// holds slot j.
 struct Selection {
   int id;        // expert id of this lane's slot, -1 if none
   float z;       // its logit
@@ -279,25 +321,26 @@ struct Selection {
   float gap;     // z_(k) - z_(k+1); +inf if only k eligible; NaN if fewer
 };
 
-// The k + 1 selection rounds and the softmax over the k selected logits.
-// Each round takes the largest remaining order key (a max reduction) and,
-// among the lanes holding it, the smallest expert id (a min reduction); the
-// (k+1)-th round only reads the runner-up for the gap.  The red_* functions
-// reduce over the lanes that hold this token's keys (a row or the whole wave);
-// `slot` is this lane's position among them.
-template <int KPL, typename MaxOp, typename MinOp, typename SumOp>
+__device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
+
+// The k + 1 selection rounds and the softmax over the k selected logits of a
+// wave that holds one token's keys, lane l those of experts q * 64 + l.  Each
+// round takes the largest remaining order key (a wave max) and the smallest
+// expert id holding it: the first set bit of the first non-empty ballot
+// (scalar work, in place of a second cross-lane reduction).  The (k+1)-th
+// round only reads the runner-up for the gap.
+template <int KPL>
 __device__ __forceinline__ Selection select_topk(uint32_t (&key)[KPL], const int (&eid)[KPL],
-                                                 int k, int slot, MaxOp red_max, MinOp red_min,
-                                                 SumOp red_sum) {
+                                                 int k, int lane) {
   Selection s{-1, 0.f, 0.f, 0.f};
   float z_first = 0.f, zk = 0.f, zk1 = 0.f;
   bool complete = true, have_next = false;
   for (int j = 0; j <= k; ++j) {
     uint32_t lm = key[0];
 #pragma unroll
-    for (int q = 1; q < KPL; ++q) lm = key[q] > lm ? key[q] : lm;
-    const uint32_t best = red_max(lm);
-    const bool found = best != 0;  // uniform over the reducing lanes
+    for (int q = 1; q < KPL; ++q) lm = umax(lm, key[q]);
+    const uint32_t best = wave_max_u32(lm);
+    const bool found = best != 0;  // uniform
     const float ze = f32_from_order_key(best);
     if (j == k) {
       if (found) {
@@ -307,13 +350,15 @@ __device__ __forceinline__ Selection select_topk(uint32_t (&key)[KPL], const int
       break;
     }
     if (!found) complete = false;
-    uint32_t cand = 0xffffffffu;
+    int e = 0;
 #pragma unroll
-    for (int q = KPL - 1; q >= 0; --q) cand = key[q] == best ? (uint32_t)eid[q] : cand;
-    const int e = (int)red_min(cand);
+    for (int q = KPL - 1; q >= 0; --q) {
+      const uint64_t holds = __ballot(key[q] == best);
+      if (holds != 0) e = q * 64 + __builtin_ctzll(holds);
+    }
     if (found) {
       if (j == 0) z_first = ze;
-      if (slot == j) {
+      if (lane == j) {
         s.id = e;
         s.z = ze;
       }
@@ -323,58 +368,36 @@ __device__ __forceinline__ Selection select_topk(uint32_t (&key)[KPL], const int
         if (eid[q] == e) key[q] = 0u;
     }
   }
-  const float ex = (slot < k && s.id >= 0) ? expf(s.z - z_first) : 0.f;
-  const float sum = red_sum(ex);
+  const float ex = (lane < k && s.id >= 0) ? expf(s.z - z_first) : 0.f;
+  const float sum = wave_sum_f32(ex);
   s.gate = s.id >= 0 ? ex / sum : 0.f;
   s.gap = !complete ? __builtin_nanf("") : (have_next ? zk - zk1 : __builtin_inff());
   return s;
 }
 
-__device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
-__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
-__device__ __forceinline__ uint32_t fadd_bits(uint32_t a, uint32_t b) {
-  return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+// A token's selection and its shared gate (0 without a shared expert).
+struct Routed {
+  Selection s;
+  float sgate;
+};
+
+template <int KPL>
+__device__ __forceinline__ void wave_experts(int lane, int (&eid)[KPL]) {
+#pragma unroll
+  for (int q = 0; q < KPL; ++q) eid[q] = q * 64 + lane;
 }
 
-// Top-k of one token per 16-lane row (four tokens per wave): lane r of the
-// row holds the keys of experts q * 16 + r.  Needs m <= 16 * KPL and k <= 16.
-// The softmax sum runs over the row with the same pairing as the wave
-// variant's first four steps; the other rows only add +0 there, so both
-// variants give identical gates.
+// Top-k of one token per wave, from its loaded logits.
 template <int KPL>
-__device__ __forceinline__ Selection select_row(const float* part, int KS, int T, const Cols& c,
-                                                int t, const float* bias,
-                                                const uint8_t* keep_mask) {
-  const int r = threadIdx.x & 15;
+__device__ __forceinline__ Routed select_wave(const LogitParts<KPL>& l, const LaneExperts<KPL>& x,
+                                              const int (&eid)[KPL], int KS, const Cols& c,
+                                              bool biased) {
   uint32_t key[KPL];
-  int eid[KPL];
-#pragma unroll
-  for (int q = 0; q < KPL; ++q) {
-    eid[q] = q * 16 + r;
-    key[q] = t < T ? logit_key(part, KS, T, c, t, eid[q], bias, keep_mask) : 0u;
-  }
-  return select_topk<KPL>(
-      key, eid, c.k, r, [](uint32_t v) { return row_reduce_u32(v, 0u, umax); },
-      [](uint32_t v) { return row_reduce_u32(v, 0xffffffffu, umin); },
-      [](float v) { return __uint_as_float(row_reduce_u32(__float_as_uint(v), 0u, fadd_bits)); });
-}
-
-// Top-k of one token per wave: lane l holds the keys of experts q * 64 + l.
-template <int KPL>
-__device__ __forceinline__ Selection select_wave(const float* part, int KS, int T, const Cols& c,
-                                                 int t, const float* bias,
-                                                 const uint8_t* keep_mask) {
-  const int lane = threadIdx.x & 63;
-  uint32_t key[KPL];
-  int eid[KPL];
-#pragma unroll
-  for (int q = 0; q < KPL; ++q) {
-    eid[q] = q * 64 + lane;
-    key[q] = logit_key(part, KS, T, c, t, eid[q], bias, keep_mask);
-  }
-  return select_topk<KPL>(
-      key, eid, c.k, lane, [](uint32_t v) { return wave_max_u32(v); },
-      [](uint32_t v) { return wave_min_u32(v); }, [](float v) { return wave_sum_f32(v); });
+  Routed o;
+  o.sgate = c.S > 0 ? shared_gate(l.gate, KS) : 0.f;
+  logit_keys<KPL>(l, x, KS, biased, key);
+  o.s = select_topk<KPL>(key, eid, c.k, threadIdx.x & 63);
+  return o;
 }
 
 // Slot `slot` of token t: a routed slot (slot < k) takes the selection,
@@ -383,22 +406,24 @@ __device__ __forceinline__ int slot_id(const Selection& s, const Cols& c, int sl
   return slot < c.k ? s.id : c.m + token_group(c, t, T) * c.S + slot - c.k;
 }
 
-__device__ __forceinline__ void store_selection(const Selection& s, int t, int T, const Cols& c,
-                                                int slot, float sgate,
-                                                int* __restrict__ topk_ids,
+__device__ __forceinline__ void store_selection(const Routed& o, int t, int T, const Cols& c,
+                                                int slot, int* __restrict__ topk_ids,
                                                 float* __restrict__ topk_w,
                                                 float* __restrict__ gap) {
   const int kout = c.k + c.S;
   if (slot < kout) {
-    topk_ids[(size_t)t * kout + slot] = slot_id(s, c, slot, t, T);
-    topk_w[(size_t)t * kout + slot] = slot < c.k ? s.gate : sgate;
+    topk_ids[(size_t)t * kout + slot] = slot_id(o.s, c, slot, t, T);
+    topk_w[(size_t)t * kout + slot] = slot < c.k ? o.s.gate : o.sgate;
   }
-  if (gap != nullptr && slot == 0) gap[t] = s.gap;
+  if (gap != nullptr && slot == 0) gap[t] = o.s.gap;
 }
 
-// ROW: one token per 16-lane row (16 tokens per 256-thread block), else one
-// token per wave (4 per block).
-template <int KPL, bool ROW>
+// One token per wave, four per block.  (Four tokens a wave, one per row of 16
+// lanes, holds 16 experts a lane where this holds 4, and the rounds' work per
+// lane counts more than the waves saved: logits and top-k of 8 tokens over
+// 256 experts took 9.9 us that way and take 7.4 us this way, of 37 tokens over
+// 128 experts 8.7 and 7.2 us, of 20 tokens over 32 experts 6.6 and 6.1 us.)
+template <int KPL>
 __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict__ part, int KS,
                                                         const float* __restrict__ bias,
                                                         const uint8_t* __restrict__ keep_mask,
@@ -406,87 +431,40 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
                                                         int* __restrict__ topk_ids,
                                                         float* __restrict__ topk_w,
                                                         float* __restrict__ gap) {
-  if (ROW) {
-    const int t = blockIdx.x * 16 + (threadIdx.x >> 4);
-    const Selection s = select_row<KPL>(part, KS, T, c, t, bias, keep_mask);
-    const float sg = (c.S > 0 && t < T) ? shared_gate(part, KS, T, c, t) : 0.f;
-    if (t < T) store_selection(s, t, T, c, threadIdx.x & 15, sg, topk_ids, topk_w, gap);
-  } else {
-    const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= T) return;  // wave-uniform
-    const Selection s = select_wave<KPL>(part, KS, T, c, t, bias, keep_mask);
-    const float sg = c.S > 0 ? shared_gate(part, KS, T, c, t) : 0.f;
-    store_selection(s, t, T, c, threadIdx.x & 63, sg, topk_ids, topk_w, gap);
-  }
+  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t >= T) return;  // wave-uniform
+  int eid[KPL];
+  wave_experts<KPL>(threadIdx.x & 63, eid);
+  const LogitParts<KPL> l = load_logits<KPL>(part, KS, T, c, t, eid);
+  const LaneExperts<KPL> x = load_experts<KPL>(c, eid, bias, keep_mask);
+  const Routed o = select_wave<KPL>(l, x, eid, KS, c, bias != nullptr);
+  store_selection(o, t, T, c, threadIdx.x & 63, topk_ids, topk_w, gap);
 }
 
-// Route + dispatch of a small batch in one 512-thread block: 16-lane row
-// i selects token i (four tokens per wave; waves without a token skip the
-// selection, so the busy waves have a SIMD each up to 16 tokens), the ids go
-// to LDS as well as to memory, and the block then builds the dispatch plan
-// from them (512 threads measured 0.4 us a step faster at one token than
-// 1024: the plan's barriers and LDS clearing cover half the waves).  Larger
-// batches take the multi-block top-k kernel and the dispatch kernel: one
-// block would serialise their selections and plan (a 1024-thread block for
-// 33-64 tokens measured 8.9 us at 64 tokens over 64 experts and 11.3 us
-// over 128, against 9.2 us for the two kernels).
-constexpr int kFusedThreads = 512;
+// Route + dispatch of a small batch in one block: wave t selects token t, the
+// ids go to LDS as well as to memory, and the first wave then builds the
+// dispatch plan from them.  Up to 16 tokens and 64 pairs, what a block of one
+// wave a token and a plan of one pair a lane hold: 9.0 us with the logits for
+// one token over 256 experts and 9.7 us for 8, against 10.4 us for the top-k
+// and dispatch kernels at 8.  Beyond, one block would serialise selections and
+// plan (two tokens a wave and a block-wide plan took 9.5 against 8.8 us at 20
+// tokens over 32 experts, and 12.8 against 10.8 us over 256).
 constexpr int kFusedMaxPool = 256;
-constexpr int kFusedMaxTokens = 32;
-constexpr int kFusedMaxK = 16;
-constexpr int kWaveFusedTokens = 4;  // one wave: 4 rows of 16 lanes, <= 64 pairs
+constexpr int kFusedMaxTokens = 16;
+constexpr int kFusedMaxPairs = 64;
 
-template <int KPL>
-__global__ __launch_bounds__(kFusedThreads) void route_select_dispatch_kernel(
-    const float* __restrict__ part, int KS, const float* __restrict__ bias,
-    const uint8_t* __restrict__ keep_mask, int T, Cols c, int* __restrict__ topk_ids,
-    float* __restrict__ topk_w, float* __restrict__ gap, int* __restrict__ counts,
-    int* __restrict__ offsets, int* __restrict__ perm, int* __restrict__ active,
-    int* __restrict__ n_active) {
-  __shared__ int ids_s[kFusedMaxTokens * kFusedMaxK];
-  __shared__ int cursor[kFusedMaxPool];
-  __shared__ int wave_base[(kFusedThreads / kWave) * kFusedMaxPool];
-  __shared__ uint8_t wave_cnt[(kFusedThreads / kWave) * kFusedMaxPool];
-  __shared__ uint32_t scan_scratch[34];
-  __shared__ int bad;
-  const int t = threadIdx.x >> 4, r = threadIdx.x & 15;
-  const int kout = c.k + c.S;
-  if ((threadIdx.x >> 6) * 4 < T) {  // wave-uniform
-    const Selection s = select_row<KPL>(part, KS, T, c, t, bias, keep_mask);
-    const float sg = (c.S > 0 && t < T) ? shared_gate(part, KS, T, c, t) : 0.f;
-    if (t < T) {
-      store_selection(s, t, T, c, r, sg, topk_ids, topk_w, gap);
-      if (r < kout) ids_s[t * kout + r] = slot_id(s, c, r, t, T);
-    }
-  }
-  __syncthreads();
-  const DispatchLds lds{cursor, wave_base, wave_cnt, scan_scratch, &bad};
-  dispatch_block(ids_s, T * kout, c.plan_m(), lds, counts, offsets, perm, active, n_active);
-}
-
-// Route + dispatch of at most 4 tokens (at most 64 pairs) in one wave: the
-// rows of 16 lanes select the tokens as above, then lane q takes pair q's id
-// and the wave builds the plan with ballots and wave scans, without a
-// barrier.  Expert i's count and offset live on lane i % 64, slot i / 64
-// (m <= 256).  The plan is the one dispatch_block builds, value for value.
-template <int KPL>
-__global__ __launch_bounds__(64) void route_select_dispatch_wave_kernel(
-    const float* __restrict__ part, int KS, const float* __restrict__ bias,
-    const uint8_t* __restrict__ keep_mask, int T, Cols c, int* __restrict__ topk_ids,
-    float* __restrict__ topk_w, float* __restrict__ gap, int* __restrict__ counts,
-    int* __restrict__ offsets, int* __restrict__ perm, int* __restrict__ active,
-    int* __restrict__ n_active) {
-  const int lane = threadIdx.x, t = lane >> 4, r = lane & 15;
-  const Selection s = select_row<KPL>(part, KS, T, c, t, bias, keep_mask);
-  const float sg = (c.S > 0 && t < T) ? shared_gate(part, KS, T, c, t) : 0.f;
-  if (t < T) store_selection(s, t, T, c, r, sg, topk_ids, topk_w, gap);
-  // the plan covers the m selectable experts and the S shared parts (<= 256
-  // in all), kout slots a token; pair q = t' * kout + j is slot j of lane
-  // 16 t' + j
-  const int kout = c.k + c.S, m = c.plan_m();
-  const int n_pairs = T * kout;
+// The plan of at most 64 pairs over at most 256 experts, by one wave with
+// ballots and wave scans, without a barrier; lane q < n_pairs holds pair q's
+// id in e.  Expert i's count and offset live on lane i % 64, slot i / 64, and
+// go between the pairs' lanes and the experts' through `lds` (kFusedMaxPool
+// words of this wave's own).  The plan is the one dispatch_block builds, value
+// for value.
+__device__ __forceinline__ void wave_plan(int e, int n_pairs, int m, volatile int* lds,
+                                          int* __restrict__ counts, int* __restrict__ offsets,
+                                          int* __restrict__ perm, int* __restrict__ active,
+                                          int* __restrict__ n_active) {
+  const int lane = threadIdx.x & 63;
   const bool valid = lane < n_pairs;
-  const int e = __shfl(slot_id(s, c, r, t, T), valid ? (lane / kout) * 16 + lane % kout : 0);
   if (__ballot(valid && (e < 0 || e >= m)) != 0) {  // the flagged plan
     for (int i = lane; i <= m; i += 64) {
       if (i < m) counts[i] = 0;
@@ -496,16 +474,20 @@ __global__ __launch_bounds__(64) void route_select_dispatch_wave_kernel(
     if (lane == 0) *n_active = -1;
     return;
   }
-  int cnt[4] = {0, 0, 0, 0};
-  for (int q = 0; q < n_pairs; ++q) {
-    const int eq = __builtin_amdgcn_readlane(e, q);
+  // the lanes of equal ids: the first of them posts their number
+  const uint64_t peers = match_peers(e, valid, id_bits(m));
+  const int rank = __popcll(peers & ((1ull << lane) - 1ull));
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (j == (eq >> 6) && lane == (eq & 63)) ++cnt[j];
-  }
+  for (int j = 0; j < 4; ++j) lds[j * 64 + lane] = 0;
+  __builtin_amdgcn_wave_barrier();
+  if (valid && rank == 0) lds[e] = __popcll(peers);
+  __builtin_amdgcn_wave_barrier();
+  int cnt[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) cnt[j] = lds[j * 64 + lane];
+  __builtin_amdgcn_wave_barrier();
   // offsets = exclusive scan of the counts, active = the experts with pairs,
   // both in expert order (slot-major)
-  int off[4] = {0, 0, 0, 0};
   uint32_t run_off = 0, run_act = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -513,10 +495,11 @@ __global__ __launch_bounds__(64) void route_select_dispatch_wave_kernel(
     const int i = j * 64 + lane;
     const uint32_t c = i < m ? (uint32_t)cnt[j] : 0u, a = c > 0 ? 1u : 0u;
     const uint32_t ic = wave_inclusive_scan_u32(c), ia = wave_inclusive_scan_u32(a);
-    off[j] = (int)(run_off + ic - c);
+    const int off = (int)(run_off + ic - c);
+    lds[i] = off;
     if (i < m) {
       counts[i] = (int)c;
-      offsets[i] = off[j];
+      offsets[i] = off;
       if (c > 0) active[run_act + ia - a] = i;
     }
     run_off += __builtin_amdgcn_readlane(ic, 63);
@@ -527,15 +510,32 @@ __global__ __launch_bounds__(64) void route_select_dispatch_wave_kernel(
     *n_active = (int)run_act;
   }
   // stable scatter: pair q goes after the earlier pairs of its expert
-  const uint64_t peers = match_peers(e, valid, id_bits(m));
-  const int rank = __popcll(peers & ((1ull << lane) - 1ull));
-  int base = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int v = __shfl(off[j], e & 63);
-    if (j == (e >> 6)) base = v;
-  }
-  if (valid) perm[base + rank] = lane;
+  __builtin_amdgcn_wave_barrier();
+  if (valid) perm[lds[e] + rank] = lane;
+}
+
+template <int KPL>
+__global__ __launch_bounds__(64 * kFusedMaxTokens) void route_select_dispatch_kernel(
+    const float* __restrict__ part, int KS, const float* __restrict__ bias,
+    const uint8_t* __restrict__ keep_mask, int T, Cols c, int* __restrict__ topk_ids,
+    float* __restrict__ topk_w, float* __restrict__ gap, int* __restrict__ counts,
+    int* __restrict__ offsets, int* __restrict__ perm, int* __restrict__ active,
+    int* __restrict__ n_active) {
+  __shared__ int ids_s[kFusedMaxPairs];
+  __shared__ int plan_s[kFusedMaxPool];
+  const int lane = threadIdx.x & 63, t = threadIdx.x >> 6;  // one wave per token
+  const int kout = c.k + c.S, n_pairs = T * kout;
+  int eid[KPL];
+  wave_experts<KPL>(lane, eid);
+  const LogitParts<KPL> l = load_logits<KPL>(part, KS, T, c, t, eid);
+  const LaneExperts<KPL> x = load_experts<KPL>(c, eid, bias, keep_mask);
+  const Routed o = select_wave<KPL>(l, x, eid, KS, c, bias != nullptr);
+  store_selection(o, t, T, c, lane, topk_ids, topk_w, gap);
+  if (lane < kout) ids_s[t * kout + lane] = slot_id(o.s, c, lane, t, T);
+  __syncthreads();
+  if (t == 0)
+    wave_plan(lane < n_pairs ? ids_s[lane] : 0, n_pairs, c.plan_m(), plan_s, counts, offsets,
+              perm, active, n_active);
 }
 
 // Split of the router contraction for T tokens and m experts: KW waves per
@@ -578,111 +578,135 @@ hipError_t launch_logits(const uint16_t* x, int T, const float* wr, int H, int m
   return hipGetLastError();
 }
 
-template <int KPL, bool ROW>
-void launch_topk_t(const float* part, int KS, const float* bias, const uint8_t* keep_mask, int T,
-                   const Cols& c, int* topk_ids, float* topk_w, float* gap, hipStream_t stream) {
-  const int per_block = ROW ? 16 : 4;
-  route_topk_kernel<KPL, ROW><<<(T + per_block - 1) / per_block, 256, 0, stream>>>(
-      part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap);
-}
-
 void launch_topk(const float* part, int KS, const float* bias, const uint8_t* keep_mask, int T,
                  const Cols& c, int* topk_ids, float* topk_w, float* gap, hipStream_t stream) {
-  // one token per 16-lane row for small batches; from 64 tokens on, one token
-  // per wave (more waves in flight) measured faster: 8.3 against 12.5 us at
-  // 4096 tokens, 2-3% of a 40-layer batch-256 step, 2 us of a batch-64 step
-  // over 128 experts
-  if (c.k + c.S <= 16 && c.m <= 256 && T < 64) {
-    const int kpl = (c.m + 15) / 16;
-    if (kpl <= 4)
-      launch_topk_t<4, true>(part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap, stream);
-    else if (kpl <= 8)
-      launch_topk_t<8, true>(part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap, stream);
-    else
-      launch_topk_t<16, true>(part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap, stream);
-    return;
-  }
-  const int kpl = (c.m + 63) / 64;
+  const int blocks = (T + 3) / 4, kpl = (c.m + 63) / 64;
+#define SW_TK(KPL)                                                                             \
+  route_topk_kernel<KPL><<<blocks, 256, 0, stream>>>(part, KS, bias, keep_mask, T, c, topk_ids, \
+                                                     topk_w, gap)
   if (kpl <= 1)
-    launch_topk_t<1, false>(part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap, stream);
+    SW_TK(1);
   else if (kpl <= 2)
-    launch_topk_t<2, false>(part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap, stream);
+    SW_TK(2);
   else if (kpl <= 4)
-    launch_topk_t<4, false>(part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap, stream);
+    SW_TK(4);
   else if (kpl <= 8)
-    launch_topk_t<8, false>(part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap, stream);
+    SW_TK(8);
   else
-    launch_topk_t<16, false>(part, KS, bias, keep_mask, T, c, topk_ids, topk_w, gap, stream);
+    SW_TK(16);
+#undef SW_TK
 }
 
 // ---------------------------------------------------------------------------
 // Routing-mass statistics (Section 2.3: an importance criterion aggregating
 // the router's gate probabilities over calibration tokens).
+//
+// Two kernels after the logits.  The first gives every wave a contiguous run
+// of tokens: the wave holds one token's logits (lane l experts q * 64 + l),
+// selects its top k as the router does, and adds its softmax and its gates
+// to per-expert sums in registers; a block adds its waves' sums in wave
+// order and writes one row of partial sums.  The second adds the rows, in an
+// order that depends on nothing but the shape.  (One thread per expert
+// walking all tokens, as this was, is one chain of T dependent exponentials
+// on 256 threads of the chip: 1672 us of a 1681 us call at 4096 tokens over
+// 256 experts, H 2048.  Now the whole call takes 44 us, 27 of them the logits,
+// and needs no dispatch plan.)
 
-// Token t's logit for expert e: the KS partials in slice order, plus bias.
-__device__ __forceinline__ float logit_value(const float* __restrict__ part, int KS, int T, int m,
-                                             int t, int e, const float* __restrict__ bias) {
-  const float* p = part + (size_t)t * m + e;
-  const size_t plane = (size_t)T * m;
-  float z = p[0];
-  for (int ks = 1; ks < KS; ++ks) z += p[ks * plane];
-  if (bias != nullptr) z += bias[e];
-  return z;
-}
+constexpr int kMassWaves = 8;        // waves per block of the first kernel
+constexpr int kMassTokens = 2;       // tokens a wave takes while blocks are left to give
+constexpr int kMassMaxBlocks = 512;  // two per compute unit
+constexpr int kMassSumRows = 16;     // row groups of the second kernel
 
-// One wave per token: the largest eligible logit and the softmax
-// denominator over the eligible experts.
-__global__ __launch_bounds__(256) void mass_token_stats_kernel(
+template <int KPL>
+__global__ __launch_bounds__(64 * kMassWaves) void mass_partial_kernel(
     const float* __restrict__ part, int KS, const float* __restrict__ bias,
-    const uint8_t* __restrict__ keep_mask, int T, int m, float* __restrict__ zmax,
-    float* __restrict__ denom) {
-  const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= T) return;  // wave-uniform
-  uint32_t best = 0u;  // order key; 0 = no eligible expert on this lane
-  for (int e = lane; e < m; e += kWave)
-    if (keep_mask == nullptr || keep_mask[e] != 0)
-      best = max(best, max(f32_order_key(logit_value(part, KS, T, m, t, e, bias)), 1u));
-  best = wave_max_u32(best);
-  const float zm = f32_from_order_key(best);
-  float s = 0.f;
-  for (int e = lane; e < m; e += kWave)
-    if (keep_mask == nullptr || keep_mask[e] != 0)
-      s += expf(logit_value(part, KS, T, m, t, e, bias) - zm);
-  s = wave_sum_f32(s);
-  if (lane == 0) {
-    zmax[t] = zm;
-    denom[t] = s;
-  }
-}
-
-// One thread per expert: the token-ordered sum of its softmax share and of
-// the gates it received (its dispatch slots in order), added to the masses.
-__global__ __launch_bounds__(256) void mass_accumulate_kernel(
-    const float* __restrict__ part, int KS, const float* __restrict__ bias,
-    const uint8_t* __restrict__ keep_mask, int T, int m, const float* __restrict__ zmax,
-    const float* __restrict__ denom, const float* __restrict__ topk_w,
-    const int* __restrict__ counts, const int* __restrict__ offsets,
-    const int* __restrict__ perm, const int* __restrict__ n_active, int n_pairs,
-    float* __restrict__ mass_softmax, float* __restrict__ mass_topk) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= m) return;
-  if (mass_softmax != nullptr && (keep_mask == nullptr || keep_mask[e] != 0)) {
-    float acc = 0.f;
-    for (int t = 0; t < T; ++t)
-      acc += expf(logit_value(part, KS, T, m, t, e, bias) - zmax[t]) / denom[t];
-    mass_softmax[e] += acc;
-  }
-  if (mass_topk != nullptr && *n_active >= 0) {
-    const int b = offsets[e], c = counts[e];
-    float acc = 0.f;
-    if (b >= 0 && c >= 0 && c <= n_pairs - b)
-      for (int i = 0; i < c; ++i) {
-        const int p = perm[b + i];
-        if (p >= 0 && p < n_pairs) acc += topk_w[p];
+    const uint8_t* __restrict__ keep_mask, int T, int m, int k, bool want_topk,
+    float* __restrict__ rows) {
+  __shared__ float red[kMassWaves][2][64 * KPL];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long long n_waves = (long long)gridDim.x * kMassWaves;
+  const long long w = (long long)blockIdx.x * kMassWaves + wave;
+  const int t_lo = (int)(w * T / n_waves), t_hi = (int)((w + 1) * T / n_waves);
+  const Cols c{m, m, k, 0, 1};
+  int eid[KPL];
+  float soft[KPL], top[KPL];
+  wave_experts<KPL>(lane, eid);
+#pragma unroll
+  for (int q = 0; q < KPL; ++q) soft[q] = top[q] = 0.f;
+  const LaneExperts<KPL> x = load_experts<KPL>(c, eid, bias, keep_mask);
+  LogitParts<KPL> next = load_logits<KPL>(part, KS, T, c, t_lo, eid);
+  for (int t = t_lo; t < t_hi; ++t) {
+    const LogitParts<KPL> now = next;
+    next = load_logits<KPL>(part, KS, T, c, t + 1, eid);  // read a token ahead
+    uint32_t key[KPL], best = 0u;  // order keys (0: ineligible)
+    float ex[KPL], sum = 0.f;
+    logit_keys<KPL>(now, x, KS, bias != nullptr, key);
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) best = umax(best, key[q]);
+    const float zm = f32_from_order_key(wave_max_u32(best));
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) {
+      ex[q] = key[q] != 0u ? expf(f32_from_order_key(key[q]) - zm) : 0.f;
+      sum += ex[q];
+    }
+    const float denom = wave_sum_f32(sum);
+#pragma unroll
+    for (int q = 0; q < KPL; ++q)
+      if (key[q] != 0u) soft[q] += ex[q] / denom;
+    if (want_topk) {  // uniform
+      const Selection s = select_topk<KPL>(key, eid, k, lane);
+      for (int j = 0; j < k; ++j) {
+        const int id = __builtin_amdgcn_readlane(s.id, j);
+        const float g =
+            __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s.gate), j));
+#pragma unroll
+        for (int q = 0; q < KPL; ++q) top[q] += eid[q] == id ? g : 0.f;
       }
-    mass_topk[e] += acc;
+    }
   }
+#pragma unroll
+  for (int q = 0; q < KPL; ++q) {
+    red[wave][0][eid[q]] = soft[q];
+    red[wave][1][eid[q]] = top[q];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 2 * m; i += 64 * kMassWaves) {
+    const int which = i >= m ? 1 : 0, e = i - which * m;
+    float v = red[0][which][e];
+#pragma unroll
+    for (int u = 1; u < kMassWaves; ++u) v += red[u][which][e];
+    rows[(size_t)blockIdx.x * 2 * m + i] = v;
+  }
+}
+
+// Adds the partial rows to the masses: blockIdx.y 0 the softmax mass, 1 the
+// top-k mass.  Thread (r, lane) sums rows r, r + kMassSumRows, ... of expert
+// blockIdx.x * 64 + lane; the row groups are then added in order.  The top-k
+// mass is left alone when fewer than k experts are eligible (every token's
+// selection then lacks a slot).
+__global__ __launch_bounds__(64 * kMassSumRows) void mass_sum_kernel(
+    const float* __restrict__ rows, int n_rows, const uint8_t* __restrict__ keep_mask, int m,
+    int k, float* __restrict__ mass_softmax, float* __restrict__ mass_topk) {
+  __shared__ float red[kMassSumRows][64];
+  const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + lane;
+  float* mass = blockIdx.y == 0 ? mass_softmax : mass_topk;
+  if (mass == nullptr) return;  // block-uniform
+  int missing = 0;              // pruned experts (of those this thread counts)
+  if (keep_mask != nullptr)
+    for (int i = threadIdx.x; i < m; i += 64 * kMassSumRows) missing += keep_mask[i] == 0 ? 1 : 0;
+  float v = 0.f;
+  if (e < m)
+    for (int i = r; i < n_rows; i += kMassSumRows)
+      v += rows[(size_t)i * 2 * m + (size_t)blockIdx.y * m + e];
+  red[r][lane] = v;
+  // m <= 64 * kMassSumRows: a thread counts at most one expert
+  const int eligible = m - __syncthreads_count(missing);
+  if (r != 0 || e >= m || (blockIdx.y == 1 && eligible < k)) return;
+  float s = red[0][lane];
+#pragma unroll
+  for (int u = 1; u < kMassSumRows; ++u) s += red[u][lane];
+  if (keep_mask == nullptr || keep_mask[e] != 0) mass[e] += s;
 }
 
 }  // namespace
@@ -694,42 +718,44 @@ size_t routing_mass_workspace_bytes(int T, int H, int m, int k) {
          3 * align_up((size_t)(m + 1) * 4, 256) + 256 + 2 * align_up((size_t)T * 4, 256);
 }
 
+// Blocks of mass_partial_kernel: kMassTokens tokens a wave until two blocks a
+// compute unit, as far as the workspace behind the logits holds their rows
+// (at least one: it holds 3 (m + 1) words).
+static int mass_blocks(int T, int m, size_t row_bytes) {
+  const long want = ((long)T + kMassWaves * kMassTokens - 1) / (kMassWaves * kMassTokens);
+  const long fit = (long)(row_bytes / ((size_t)2 * m * sizeof(float)));
+  return (int)std::max(1L, std::min({want, fit, (long)kMassMaxBlocks}));
+}
+
 hipError_t launch_routing_mass(const uint16_t* x, int T, const float* wr, const float* bias,
                                const uint8_t* keep_mask, int H, int m, int k, float* mass_softmax,
                                float* mass_topk, void* workspace, hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  char* p = static_cast<char*>(workspace);
-  const size_t P = (size_t)T * k;
-  float* part = reinterpret_cast<float*>(p);
-  p += route_workspace_bytes(T, H, m, k);
-  int* ids = reinterpret_cast<int*>(p);
-  p += align_up(P * 4, 256);
-  float* w = reinterpret_cast<float*>(p);
-  p += align_up(P * 4, 256);
-  int* perm = reinterpret_cast<int*>(p);
-  p += align_up(P * 4, 256);
-  int* counts = reinterpret_cast<int*>(p);
-  p += align_up((size_t)(m + 1) * 4, 256);
-  int* offsets = reinterpret_cast<int*>(p);
-  p += align_up((size_t)(m + 1) * 4, 256);
-  int* active = reinterpret_cast<int*>(p);
-  p += align_up((size_t)(m + 1) * 4, 256);
-  int* n_active = reinterpret_cast<int*>(p);
-  p += 256;
-  float* zmax = reinterpret_cast<float*>(p);
-  p += align_up((size_t)T * 4, 256);
-  float* denom = reinterpret_cast<float*>(p);
-  hipError_t err = launch_route_dispatch(x, T, wr, bias, keep_mask, H, m, k, ids, w, nullptr,
-                                         counts, offsets, perm, active, n_active, part, stream);
+  float* part = static_cast<float*>(workspace);
+  const size_t logit_bytes = route_workspace_bytes(T, H, m, k);
+  float* rows = reinterpret_cast<float*>(static_cast<char*>(workspace) + logit_bytes);
+  const int n_rows = mass_blocks(T, m, routing_mass_workspace_bytes(T, H, m, k) - logit_bytes);
+  const LogitsSplit sp = logits_split(T, H, m);
+  hipError_t err = launch_logits(x, T, wr, H, m, part, sp, stream);
   if (err != hipSuccess) return err;
-  const int KS = logits_split(T, H, m).ks;
-  mass_token_stats_kernel<<<(T + 3) / 4, 256, 0, stream>>>(part, KS, bias, keep_mask, T, m, zmax,
-                                                           denom);
+#define SW_MP(KPL)                                                                             \
+  mass_partial_kernel<KPL><<<n_rows, 64 * kMassWaves, 0, stream>>>(                               \
+      part, sp.ks, bias, keep_mask, T, m, k, mass_topk != nullptr, rows)
+  if (m <= 64)
+    SW_MP(1);
+  else if (m <= 128)
+    SW_MP(2);
+  else if (m <= 256)
+    SW_MP(4);
+  else if (m <= 512)
+    SW_MP(8);
+  else
+    SW_MP(16);
+#undef SW_MP
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  mass_accumulate_kernel<<<(m + 255) / 256, 256, 0, stream>>>(
-      part, KS, bias, keep_mask, T, m, zmax, denom, w, counts, offsets, perm, n_active,
-      (int)P, mass_softmax, mass_topk);
+  mass_sum_kernel<<<dim3((m + 63) / 64, 2), 64 * kMassSumRows, 0, stream>>>(
+      rows, n_rows, keep_mask, m, k, mass_softmax, mass_topk);
   return hipGetLastError();
 }
 
@@ -783,7 +809,8 @@ hipError_t launch_route_select(const uint16_t* x, int T, const float* wr, const 
 }
 
 bool fused_route_dispatch_supported(int T, int m, int k, int S, int R) {
-  return T > 0 && T <= kFusedMaxTokens && m + R * S <= kFusedMaxPool && k + S <= kFusedMaxK;
+  return T > 0 && T <= kFusedMaxTokens && m + R * S <= kFusedMaxPool &&
+         T * (k + S) <= kFusedMaxPairs;
 }
 
 hipError_t launch_route_dispatch(const uint16_t* x, int T, const float* wr, const float* bias,
@@ -806,31 +833,17 @@ hipError_t launch_route_dispatch(const uint16_t* x, int T, const float* wr, cons
   const LogitsSplit sp = logits_split(T, H, c.ld);
   hipError_t err = launch_logits(x, T, wr, H, c.ld, part, sp, stream);
   if (err != hipSuccess) return err;
-  const int kpl = (m + 15) / 16;
-  if (T <= kWaveFusedTokens) {
-#define SW_WF(KPL)                                                                             \
-  route_select_dispatch_wave_kernel<KPL><<<1, 64, 0, stream>>>(part, sp.ks, bias, keep_mask, T, c, \
-                                                               topk_ids, topk_w, gap, counts,      \
-                                                               offsets, perm, active, n_active)
-    if (kpl <= 4)
-      SW_WF(4);
-    else if (kpl <= 8)
-      SW_WF(8);
-    else
-      SW_WF(16);
-#undef SW_WF
-    return hipGetLastError();
-  }
+  const int kpl = (m + 63) / 64;
 #define SW_FD(KPL)                                                                             \
-  route_select_dispatch_kernel<KPL><<<1, kFusedThreads, 0, stream>>>(                             \
+  route_select_dispatch_kernel<KPL><<<1, 64 * T, 0, stream>>>(                                    \
       part, sp.ks, bias, keep_mask, T, c, topk_ids, topk_w, gap, counts, offsets, perm, active,   \
       n_active)
-  if (kpl <= 4)
-    SW_FD(4);
-  else if (kpl <= 8)
-    SW_FD(8);
+  if (kpl <= 1)
+    SW_FD(1);
+  else if (kpl <= 2)
+    SW_FD(2);
   else
-    SW_FD(16);
+    SW_FD(4);
 #undef SW_FD
   return hipGetLastError();
 }

@@ -164,10 +164,6 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return wave_reduce_u32(v, 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
 }
 
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-  return wave_reduce_u32(v, 0xffffffffu, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
-}
-
 __device__ __forceinline__ float wave_sum_f32(float v) {
   const uint32_t r = wave_reduce_u32(__float_as_uint(v), 0u, [](uint32_t a, uint32_t b) {
     return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));

@@ -1,0 +1,117 @@
+"""GPU kernels and dispatch branches at the sizes where they can go wrong:
+edges of tiles, remainders, the smallest and largest of a range.  Whole
+layers at the usual sizes are in test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+import oracle
+from parity import GAP_TOL, compare_routing, near_tie_tokens
+from test_gpu_parity import dev, host, small_layer
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sw():
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    from paper_2609_34117_amd import slimwise
+
+    return slimwise
+
+
+# --------------------------------------------------------------------------
+# routing mass: waves without a token, uneven token runs, every experts-a-lane
+# count, experts past the last full lane, the block cap set by the workspace
+# (few pairs: m 1000, k 1), fewer eligible experts than k
+
+@pytest.mark.parametrize("hidden,m,k,tokens,eligible", [
+    (64, 64, 8, 1, 64),
+    (128, 65, 3, 33, 65),
+    (256, 128, 32, 130, 40),
+    (256, 300, 4, 97, 300),
+    (256, 1000, 1, 1300, 1000),
+    (512, 256, 8, 4097, 256),
+    (256, 96, 8, 50, 5),
+])
+def test_routing_mass_edges(sw, hidden, m, k, tokens, eligible):
+    cfg, L, D = small_layer(hidden, m, k, 32, tokens, seed=31)
+    mask = None
+    if eligible < m:
+        mask = np.zeros(m, np.uint8)
+        mask[np.random.default_rng(5).permutation(m)[:eligible]] = 1
+    start = np.linspace(0.5, 2.0, m).astype(np.float32)
+    mass = (dev(start), dev(start))
+    sw.sw_moe_routing_mass(D["x"], D["wr"], k, keep_mask=None if mask is None else dev(mask),
+                           mass=mass)
+    ms, mt = host(mass[0]) - start, host(mass[1]) - start
+    z = oracle.route(L["x"], L["wr"], min(k, eligible), keep_mask=mask, want_logits=True)[3]
+    z = z.astype(np.float64)
+    if mask is not None:
+        z[:, mask == 0] = -np.inf
+    p = np.exp(z - z.max(1, keepdims=True))
+    o_ms = (p / p.sum(1, keepdims=True)).sum(0)
+    # a logit off by GAP_TOL moves a share by twice that; the sums round at
+    # 2^-24 of the running mass, here and in `start` + mass
+    tol = 2 * GAP_TOL * o_ms + 2.0 ** -22 * (o_ms + 2.0)
+    assert np.all(np.abs(ms - o_ms) <= tol)
+    if eligible < k:
+        assert np.array_equal(host(mass[1]), start)
+        return
+    o_mt = np.zeros(m)
+    order = np.argsort(-z, axis=1, kind="stable")[:, :k]
+    w = np.exp(np.take_along_axis(z, order, 1) - z.max(1, keepdims=True))
+    np.add.at(o_mt, order, w / w.sum(1, keepdims=True))
+    n_near = int(near_tie_tokens(z, mask, k).sum())
+    assert np.all(np.abs(mt - o_mt) <= 2 * GAP_TOL * o_mt + 2.0 ** -22 * (o_mt + 2.0) + n_near)
+
+
+# --------------------------------------------------------------------------
+# selection and plan: one wave a token and one plan wave up to 16 tokens and 64
+# pairs, the separate kernels past either edge; 1 to 16 experts a lane, pools
+# that end inside a wave, masks and biases
+
+def plan_of(ids, m):
+    """(counts, offsets, perm, active) of the pairs' ids, by a stable sort."""
+    flat = np.asarray(ids).reshape(-1)
+    counts = np.bincount(flat, minlength=m)
+    return (counts, np.concatenate([[0], np.cumsum(counts)]), np.argsort(flat, kind="stable"),
+            np.nonzero(counts)[0])
+
+
+def check_plan(plan, ids, m):
+    counts, offsets, perm, active = plan_of(ids, m)
+    assert int(plan.n_active.item()) == len(active)
+    assert np.array_equal(host(plan.counts), counts)
+    assert np.array_equal(host(plan.offsets), offsets)
+    assert np.array_equal(host(plan.perm)[: len(perm)], perm)
+    assert np.array_equal(host(plan.active)[: len(active)], active)
+
+
+@pytest.mark.parametrize("m,k,tokens,masked,biased", [
+    (256, 4, 16, True, True),     # 64 pairs on 16 waves
+    (256, 8, 8, False, False),    # 64 pairs on 8
+    (256, 16, 4, True, False),    # 64 pairs on 4
+    (16, 16, 1, False, False),    # k = m: an infinite gap
+    (65, 3, 16, False, True),     # the pool ends inside the second expert a lane
+    (256, 8, 9, True, True),      # 72 pairs
+    (128, 1, 17, False, False),   # 17 tokens
+    (257, 8, 2, False, True),     # past the fused pool
+    (1000, 2, 5, True, True),     # 16 experts a lane
+])
+def test_selection_and_plan_edges(sw, m, k, tokens, masked, biased):
+    cfg, L, D = small_layer(512, m, k, 32, tokens, seed=41)
+    rng = np.random.default_rng([41, m, k])
+    mask = None
+    if masked:
+        mask = np.zeros(m, np.uint8)
+        mask[rng.permutation(m)[: max(k, m // 2)]] = 1
+    bias = (0.5 * rng.standard_normal(m)).astype(np.float32) if biased else None
+    ids, w, gap, plan = sw.sw_moe_route_dispatch(
+        D["x"], D["wr"], k, keep_mask=None if mask is None else dev(mask),
+        bias=None if bias is None else dev(bias))
+    o_ids, o_w, o_gap, o_z = oracle.route(L["x"], L["wr"], k, keep_mask=mask, bias=bias,
+                                          want_logits=True)
+    compare_routing(host(ids), host(w), o_ids, o_w, o_z, mask, k, g_gap=host(gap), o_gap=o_gap)
+    check_plan(plan, host(ids), m)
