@@ -115,3 +115,23 @@ def test_selection_and_plan_edges(sw, m, k, tokens, masked, biased):
                                           want_logits=True)
     compare_routing(host(ids), host(w), o_ids, o_w, o_z, mask, k, g_gap=host(gap), o_gap=o_gap)
     check_plan(plan, host(ids), m)
+
+
+# the one-block plan: one pair, part of a run, both block sizes at their largest
+# pools and pair counts, every pair on one expert, then the first size past it;
+# an id out of range on the last pair
+
+@pytest.mark.parametrize("m,pairs,spread", [
+    (1, 1, 1), (7, 63, 7), (512, 1024, 512), (513, 1024, 513), (512, 1025, 3), (1024, 2048, 1024),
+    (300, 2047, 1), (300, 2049, 300),
+])
+def test_dispatch_plan_edges(sw, m, pairs, spread):
+    rng = np.random.default_rng([43, m, pairs])
+    ids = (rng.integers(0, spread, (pairs, 1)) + (m - spread)).astype(np.int32)
+    check_plan(sw.sw_moe_dispatch(dev(ids), m), ids, m)
+    for bad in (m, -1):
+        ids[-1] = bad
+        plan = sw.sw_moe_dispatch(dev(ids), m)
+        assert int(plan.n_active.item()) == -1
+        assert not host(plan.counts).any() and not host(plan.offsets).any()
+        assert np.array_equal(host(plan.perm), np.arange(pairs))
