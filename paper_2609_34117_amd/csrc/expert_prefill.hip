@@ -157,11 +157,6 @@ constexpr int gu_segs() {  // direct-to-LDS loads per wave per chunk
   return kSegs;
 }
 
-// s_waitcnt immediates: at most n vector-memory loads outstanding (expcnt
-// and lgkmcnt left alone), and the same with every LDS access done
-constexpr int vmcnt_at_most(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
-constexpr int vmcnt_at_most_lds_done(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
-
 template <bool kTiled, int D, int NBK>
 __device__ __forceinline__ void gu_pass(__amdgpu_buffer_rsrc_t w, __amdgpu_buffer_rsrc_t xr,
                                         const int (&ib)[kTpw], const int* tok,

@@ -83,12 +83,7 @@ __device__ __forceinline__ void stage_row(__amdgpu_buffer_rsrc_t r, uint32_t src
   }
 }
 
-// s_waitcnt immediates (gfx9 encoding): at most n vector-memory operations
-// outstanding, expcnt and lgkmcnt left alone
-constexpr int vmcnt_at_most(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 constexpr int kVmcntZero = vmcnt_at_most(0);
-// ... and every LDS access of this wave done
-constexpr int vmcnt_at_most_lds_done(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 // only this wave's LDS accesses done (vmcnt at its maximum)
 constexpr int kLdsDone = vmcnt_at_most_lds_done(63);
 

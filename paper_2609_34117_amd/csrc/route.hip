@@ -97,109 +97,166 @@ __global__ __launch_bounds__(64 * KW) void route_logits_kernel(const uint16_t* _
   }
 }
 
-// Router logits of prefill-sized batches: a block of 4 waves computes a
-// 64-token x 64-expert tile over slice blockIdx.z of H (KS = gridDim.z
-// slices of whole 128-column chunks, so that several blocks share a compute
-// unit and hide each other's load latency).  The tile's x
-// rows are staged in LDS one 128-column chunk at a time (double-buffered),
-// so each token row is read once per 64 experts instead of once per 16, and
-// wave w reads the router rows of experts e0 + 16 w .. e0 + 16 w + 15
-// directly: every router fragment, split into its three bf16 pieces once,
-// feeds the 4 token blocks of the tile.  Same exact three-piece products as
-// route_logits_kernel, accumulated over H in ascending order.
-constexpr int kWideT = 64, kWideE = 64, kWideKc = 128, kWideRow = kWideKc + 8;
+// Router logits of prefill-sized batches: a block of 8 waves computes 32 TF
+// tokens x 64 experts over slice blockIdx.z of H (KS = gridDim.z slices of
+// whole 128-column units); wave w takes experts e0 + 16 (w % 4) .. + 15 of the
+// token half w / 4.  Same exact three-piece products as route_logits_kernel,
+// accumulated over H in ascending order.
+//
+// The matrix cores need 5 us of 3 bf16 MFMAs a product at 4096 tokens x 256
+// experts; what bounds the loop is how the operands arrive.  An MFMA operand
+// wants consecutive lanes in different rows, and a load like that costs the
+// compute unit's address path one cycle per lane (64 a load, against 8 to 16
+// where consecutive lanes share a line: 52K of the 70K cycles of the former
+// kernel, which read the router so).  So both operands go straight into LDS,
+// 8 or 16 consecutive lanes a row (buffer loads with the LDS bit), three
+// 64-column chunks ahead in a four-slot ring, and the operand reads pick
+// their rows there.  A router fragment is split into its three pieces once
+// for TF token blocks.  At 4096 tokens x 256 experts, H 2048, kernel trace:
+// 27 us with the router read into registers (64-token tiles of 4 waves),
+// 29 us so with the x ring and 128-token tiles, 19 us with both rings; with
+// 64-token tiles and both rings (the router read twice as often) 27 us.
+constexpr int kWideE = 64, kWideKc = 128;    // experts a block, columns of a slice's unit
+constexpr int kWideWaves = 8, kWideAhead = 3, kWideSlots = kWideAhead + 1;
+constexpr int kWideCols = 64;                // columns of a chunk
+constexpr int kWideSteps = kWideCols / 32;   // MFMA steps a chunk
 
-__global__ __launch_bounds__(256) void route_logits_wide_kernel(const uint16_t* __restrict__ x,
-                                                               const float* __restrict__ wr,
-                                                               float* __restrict__ part, int T,
-                                                               int H, int m) {
-  __shared__ uint16_t xs[2][kWideT * kWideRow];
-  const int t0 = blockIdx.x * kWideT, e0 = blockIdx.y * kWideE;
+// The 16-byte pieces of a staged row sit in XOR-swizzled places, so that the
+// operand reads hit distinct banks: 8 pieces a 128-byte x row, 16 a 256-byte
+// router row.  (A 16-lane phase of a 128-bit LDS read covers rows 0-3 and 12-15
+// of one piece and rows 4-11 of the next k-group's: a swizzle that also mixes in
+// row / 8 counted one conflict cycle for every two reads, this one none.)
+__device__ __forceinline__ int wide_x_place(int row, int piece) {
+  return piece ^ (row & 7);
+}
+__device__ __forceinline__ int wide_w_place(int row, int piece) { return piece ^ (row & 15); }
+
+template <int TF>
+__global__ __launch_bounds__(64 * kWideWaves) void route_logits_wide_kernel(
+    const uint16_t* __restrict__ x, const float* __restrict__ wr, float* __restrict__ part, int T,
+    int H, int m) {
+  constexpr int kTok = 32 * TF;                 // tokens a block
+  constexpr int kXSegs = kTok / 8 / kWideWaves;   // 1 KiB x loads (8 rows) a wave and chunk
+  constexpr int kWSegs = kWideE / 4 / kWideWaves;  // 1 KiB router loads (4 rows)
+  static_assert(kTok % (8 * kWideWaves) == 0 && kWideE % (4 * kWideWaves) == 0,
+                "whole rounds of segments");
+  constexpr int kX = kTok * kWideCols, kSlot = kX + 2 * kWideE * kWideCols;  // in 16-bit words
+  __shared__ __attribute__((aligned(1024))) uint16_t ring0[kSlot];
+  __shared__ __attribute__((aligned(1024))) uint16_t ring1[kSlot];
+  __shared__ __attribute__((aligned(1024))) uint16_t ring2[kSlot];
+  __shared__ __attribute__((aligned(1024))) uint16_t ring3[kSlot];
+  const int t0 = blockIdx.x * kTok, e0 = blockIdx.y * kWideE;
   const int ks = blockIdx.z, KS = gridDim.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int r = lane & 15, kg = lane >> 4;
   const auto w_rsrc = make_rsrc(wr, 4u * (uint32_t)m * (uint32_t)H);
   const auto x_rsrc = make_rsrc(x, 2u * (uint32_t)T * (uint32_t)H);
-  const int e = e0 + wave * 16 + r;
-  const uint32_t w_row = (uint32_t)e * H * 4u;
+  const int eg = (wave & 3) * 16, half = wave >> 2;
   const int all = H / kWideKc;
-  const int c_lo = (ks * all) / KS, c_hi = ((ks + 1) * all) / KS;
+  const int c_lo = ((ks * all) / KS) * (kWideKc / kWideCols);
+  const int n = (((ks + 1) * all) / KS) * (kWideKc / kWideCols) - c_lo;  // chunks, an even number
+  // source offsets of this lane's piece of each segment; a row past the batch
+  // or the pool reads out of range in every chunk (at most a row's bytes are
+  // added to 2^31, still past the resource)
+  uint32_t x_off[kXSegs], w_off[kWSegs];
+#pragma unroll
+  for (int j = 0; j < kXSegs; ++j) {
+    const int row = (wave + j * kWideWaves) * 8 + (lane >> 3);
+    const int piece = wide_x_place(row, lane & 7);
+    x_off[j] = t0 + row < T
+                   ? ((uint32_t)(t0 + row) * H + (uint32_t)(c_lo * kWideCols + piece * 8)) * 2u
+                   : kOutOfRange;
+  }
+#pragma unroll
+  for (int j = 0; j < kWSegs; ++j) {
+    const int row = (wave + j * kWideWaves) * 4 + (lane >> 4);
+    const int piece = wide_w_place(row, lane & 15);
+    w_off[j] = e0 + row < m
+                   ? ((uint32_t)(e0 + row) * H + (uint32_t)(c_lo * kWideCols + piece * 4)) * 4u
+                   : kOutOfRange;
+  }
+  auto slot = [&](int k) { return k == 0 ? ring0 : k == 1 ? ring1 : k == 2 ? ring2 : ring3; };
+  // chunk c into ring slot k = c % kWideSlots
+  auto stage = [&](int c, int k) {
+#pragma unroll
+    for (int j = 0; j < kXSegs; ++j)
+      buf_ld128_lds(x_rsrc, x_off[j] + (uint32_t)(c * kWideCols * 2),
+                    slot(k) + (wave + j * kWideWaves) * 512);
+#pragma unroll
+    for (int j = 0; j < kWSegs; ++j)
+      buf_ld128_lds(w_rsrc, w_off[j] + (uint32_t)(c * kWideCols * 4),
+                    slot(k) + kX + (wave + j * kWideWaves) * 512);
+    __builtin_amdgcn_sched_barrier(0);  // ahead of the chunk's arithmetic
+  };
+  // this lane's operand places (in 16-bit words), per step
+  int b_place[kWideSteps], w_place[kWideSteps][2];
+#pragma unroll
+  for (int st = 0; st < kWideSteps; ++st) {
+    b_place[st] = (half * 16 * TF + r) * kWideCols + wide_x_place(r, st * 4 + kg) * 8;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      w_place[st][i] = kX + (eg + r) * 2 * kWideCols + wide_w_place(r, st * 8 + kg * 2 + i) * 8;
+  }
 
-  // chunk c of the tile's x: 64 rows x 16 pieces of 8 columns, 4 per thread
-  auto stage_load = [&](int c, u32x4 (&v)[4]) {
+  f32x4 acc[TF];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = (int)threadIdx.x + j * 256, row = i >> 4, c8 = i & 15;
-      const int t = t0 + row;
-      v[j] = buf_ld128(x_rsrc, t < T ? ((uint32_t)t * H + (uint32_t)(c * kWideKc + c8 * 8)) * 2u
-                                     : kOutOfRange);
-    }
-  };
-  auto stage_store = [&](uint16_t* buf, const u32x4 (&v)[4]) {
+  for (int nb = 0; nb < TF; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int i = (int)threadIdx.x + j * 256;
-      *reinterpret_cast<u32x4*>(buf + (i >> 4) * kWideRow + (i & 15) * 8) = v[j];
-    }
-  };
-  auto w_issue = [&](int c, u32x4 (&wa)[4], u32x4 (&wb)[4]) {
+  for (int c = 0; c < kWideAhead; ++c) stage(c, c);
+  // Loads issued after chunk c's when chunk c is about to be read: the next
+  // kWideAhead - 1 chunks'.  Chunks past the slice's end are staged like any
+  // other (into slots never read again), so the count holds to the end.
+  constexpr int kAfter = (kWideAhead - 1) * (kXSegs + kWSegs);
+  for (int c0 = 0; c0 < n; c0 += kWideSlots) {
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      const uint32_t off =
-          e < m ? w_row + (uint32_t)(c * kWideKc + st * 32 + kg * 8) * 4u : kOutOfRange;
-      wa[st] = buf_ld128(w_rsrc, off);
-      wb[st] = buf_ld128(w_rsrc, off == kOutOfRange ? kOutOfRange : off + 16u);
-    }
-  };
-
-  f32x4 acc[4];
+    for (int d = 0; d < kWideSlots; ++d) {
+      if (d == 2 && c0 + 2 >= n) break;  // n is even
+      // this wave's part of chunk c0 + d landed and its reads of the chunk
+      // before are done; then so are every wave's, and that slot is free
+      __builtin_amdgcn_s_waitcnt(vmcnt_at_most_lds_done(kAfter));
+      __builtin_amdgcn_s_barrier();
+      stage(c0 + d + kWideAhead, (d + kWideAhead) % kWideSlots);
+      const uint16_t* buf = slot(d);
+      // every operand read of the chunk goes out before the splits, and the
+      // MFMAs run piece by piece over TF independent accumulators
+      u32x4 w[kWideSteps][2], b[kWideSteps][TF];
 #pragma unroll
-  for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  u32x4 v[4], wa[4], wb[4], na[4], nbw[4];
-  stage_load(c_lo, v);
-  w_issue(c_lo, wa, wb);
-  stage_store(xs[c_lo & 1], v);
-  for (int c = c_lo; c < c_hi; ++c) {
-    __syncthreads();  // chunk c is in LDS; the other buffer is free
-    const bool more = c + 1 < c_hi;
-    if (more) {
-      stage_load(c + 1, v);
-      w_issue(c + 1, na, nbw);
-    }
-    const uint16_t* buf = xs[c & 1];
+      for (int st = 0; st < kWideSteps; ++st) {
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      u32x4 hi, mid, lo;
-      split3_bf16x8(__builtin_bit_cast(float4, wa[st]), __builtin_bit_cast(float4, wb[st]), hi, mid,
-                    lo);
+        for (int i = 0; i < 2; ++i)
+          w[st][i] = *reinterpret_cast<const u32x4*>(buf + w_place[st][i]);
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) {
-        const u32x4 b = *reinterpret_cast<const u32x4*>(buf + (nb * 16 + r) * kWideRow + st * 32 +
-                                                        kg * 8);
-        acc[nb] = mfma_16x16x32(hi, b, acc[nb]);
-        acc[nb] = mfma_16x16x32(mid, b, acc[nb]);
-        acc[nb] = mfma_16x16x32(lo, b, acc[nb]);
+        for (int nb = 0; nb < TF; ++nb)
+          b[st][nb] = *reinterpret_cast<const u32x4*>(buf + b_place[st] + nb * 16 * kWideCols);
       }
-    }
-    if (more) {
-      stage_store(xs[(c + 1) & 1], v);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        wa[st] = na[st];
-        wb[st] = nbw[st];
+      for (int st = 0; st < kWideSteps; ++st) {
+        u32x4 w3[3];
+        split3_bf16x8(__builtin_bit_cast(float4, w[st][0]), __builtin_bit_cast(float4, w[st][1]),
+                      w3[0], w3[1], w3[2]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+          for (int nb = 0; nb < TF; ++nb) acc[nb] = mfma_16x16x32(w3[p], b[st][nb], acc[nb]);
       }
     }
   }
-  // acc[nb][i]: expert e0 + 16 wave + 4 kg + i, token t0 + 16 nb + r
+  __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));  // the loads past the end landed in LDS
+  // acc[nb][i]: expert e0 + eg + 4 kg + i, token t0 + 16 (half TF + nb) + r
+  const int e = e0 + eg + 4 * kg;
 #pragma unroll
-  for (int nb = 0; nb < 4; ++nb) {
-    const int t = t0 + nb * 16 + r;
+  for (int nb = 0; nb < TF; ++nb) {
+    const int t = t0 + (half * TF + nb) * 16 + r;
     if (t < T) {
-      float* dst = part + ((size_t)ks * T + t) * m;
+      float* dst = part + ((size_t)ks * T + t) * m + e;
+      if ((m & 3) == 0) {  // whole 16-byte groups of experts
+        if (e < m) *reinterpret_cast<f32x4*>(dst) = acc[nb];
+      } else {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ee = e0 + wave * 16 + 4 * kg + i;
-        if (ee < m) dst[ee] = acc[nb][i];
+        for (int i = 0; i < 4; ++i)
+          if (e + i < m) dst[i] = acc[nb][i];
       }
     }
   }
@@ -553,8 +610,8 @@ LogitsSplit logits_split(int T, int H, int m) {
   const long tiles = (long)((T + 15) / 16) * ((m + 15) / 16);
   if (tiles >= 1024) {
     if (H % kWideKc != 0) return {2, 1, false};
-    // >= 8 chunks a slice: at 4096 tokens, 2 slices of 8 chunks measured
-    // faster than 4 of 4, 3 of 5-6 or one of 16
+    // slices of at least 8 units: at 4096 tokens over 256 experts that is one
+    // block a compute unit (and fewer slices are fewer partials to re-read)
     return {4, std::min(kMaxSplit, std::max(1, H / kWideKc / 8)), true};
   }
   const int nsteps = (H + 31) / 32;
@@ -566,8 +623,8 @@ LogitsSplit logits_split(int T, int H, int m) {
 hipError_t launch_logits(const uint16_t* x, int T, const float* wr, int H, int m, float* part,
                          const LogitsSplit& sp, hipStream_t stream) {
   if (sp.wide) {
-    const dim3 wgrid((T + kWideT - 1) / kWideT, (m + kWideE - 1) / kWideE, sp.ks);
-    route_logits_wide_kernel<<<wgrid, 256, 0, stream>>>(x, wr, part, T, H, m);
+    const dim3 wgrid((T + 127) / 128, (m + kWideE - 1) / kWideE, sp.ks);
+    route_logits_wide_kernel<4><<<wgrid, 64 * kWideWaves, 0, stream>>>(x, wr, part, T, H, m);
     return hipGetLastError();
   }
   const dim3 grid((T + 15) / 16, (m + 15) / 16, sp.ks);

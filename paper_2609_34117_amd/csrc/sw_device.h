@@ -53,6 +53,21 @@ __device__ __forceinline__ uint32_t buf_ld32(__amdgpu_buffer_rsrc_t r, uint32_t 
   return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
 }
 
+// 16 bytes a lane straight into LDS: lane l's go to dst + 16 l (dst is
+// wave-uniform; out of range: zeros).  The compiler does not track the LDS
+// write: wait for vmcnt before the bytes are read.
+__device__ __forceinline__ void buf_ld128_lds(__amdgpu_buffer_rsrc_t r, uint32_t off,
+                                              uint16_t* dst) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, off,
+                                           0, 0, 0);
+}
+
+// s_waitcnt immediates (gfx9 encoding): at most n vector-memory operations
+// outstanding, expcnt and lgkmcnt left alone; and the same with every LDS
+// access of this wave done
+constexpr int vmcnt_at_most(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+constexpr int vmcnt_at_most_lds_done(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
+
 // D = A(16x32) * B(32x16) + C on the bf16 matrix cores, fp32 accumulate.
 // Lane l supplies A row (l % 16), B column (l % 16), and the 8-wide k-group
 // (l / 16) of both; D row 4*(l/16)+i, column l%16 lands in D[i].

@@ -135,3 +135,19 @@ def test_dispatch_plan_edges(sw, m, pairs, spread):
         assert int(plan.n_active.item()) == -1
         assert not host(plan.counts).any() and not host(plan.offsets).any()
         assert np.array_equal(host(plan.perm), np.arange(pairs))
+
+
+# --------------------------------------------------------------------------
+# prefill-sized router logits: token tiles and expert tiles that end inside a
+# block, experts that are not a multiple of four (scalar stores), one to three
+# slices of H, a slice of two chunks and one that ends in the middle of the ring
+
+@pytest.mark.parametrize("hidden,m,tokens", [
+    (128, 1000, 261), (256, 129, 1900), (1152, 64, 4100), (3072, 250, 1025),
+])
+def test_wide_logits_edges(sw, hidden, m, tokens):
+    k = 4
+    cfg, L, D = small_layer(hidden, m, k, 32, tokens, seed=47)
+    ids, w, gap = sw.sw_moe_route(D["x"], D["wr"], k)
+    o_ids, o_w, o_gap, o_z = oracle.route(L["x"], L["wr"], k, want_logits=True)
+    compare_routing(host(ids), host(w), o_ids, o_w, o_z, None, k, g_gap=host(gap), o_gap=o_gap)
