@@ -6,21 +6,37 @@
 // contraction and stream each 16-row tile once per 32-token pass; with
 // ~128 tokens per expert that would re-stream every weight four times.
 // Here the loop order is inverted:
-//   - a unit is (active expert, group of 16 row tiles), two tiles per wave;
-//     a persistent grid of one 8-wave block per compute unit walks the units,
-//     each XCD taking a contiguous run of every round's units (an expert's
-//     units then share one L2 for its gathered activations);
+//   - a unit is (active expert, group of 16 row tiles); a persistent grid of
+//     one 8-wave block per compute unit walks the units, each XCD taking a
+//     contiguous run of every round's units (an expert's units then share one
+//     L2 for its gathered activations);
 //   - a pass covers up to 160 of the expert's tokens (10 MFMA column
-//     blocks), so a unit streams its weights once per pass, normally once;
-//   - the contraction runs in chunks of K: the activations of the pass are
-//     staged chunk by chunk through a double-buffered LDS ring (the loads of
-//     chunk c + 1 go out before chunk c is computed and land in LDS after),
-//     while the weight chunks stream through a register pipeline (two
-//     chunks deep for gate/up, three for down) in the same fragment-major
-//     layout as the decode kernels;
-//   - every B fragment read from LDS feeds the MFMAs of both of the wave's
-//     tiles, halving LDS traffic per MFMA.
+//     blocks), so a unit streams its weights once per pass, normally once.
+//     Wave w computes row tiles 4 (w % 4) .. + 3 for half of the pass's column
+//     blocks (w / 4), so an operand read from LDS feeds 4 or 5 MFMAs;
+//   - the contraction runs in chunks of 32 or 64 columns.  Weights and
+//     activations both go straight from memory into an LDS ring (buffer loads
+//     with the LDS bit) that runs some chunks ahead of the one computed.  Such
+//     a load holds no register and no wait of the compiler's, so the ring runs
+//     on across the end of a pass: the last chunks of one
+//     pass are computed, and its results stored, while the first chunks of
+//     the next (its expert, pairs and rows looked up a few chunks earlier)
+//     are already on their way.
 // Each output accumulates over K in the same order as the decode kernels.
+//
+// What bounds it (4096 tokens, 256 experts, H 2048, I 512, top-8: 137 GFLOP of
+// gate/up products, 137 of down's over two planes, 1.6 and 0.8 GB of weights):
+// gate/up with its loads alone runs 179 us for the weights (6 TB/s) and 192
+// with the activations, its LDS reads and MFMAs alone about 180, so that
+// neither can hide the other's last part; down's loads alone are 96 us, the
+// rest MFMAs (the planes double them), LDS reads and 268 MB of results.
+// Before, the weights came through registers one 64-column chunk ahead, two
+// row tiles a wave (an LDS operand fed two MFMAs), each pass began with an
+// empty pipeline and results were stored a token per lane.  Before -> now:
+// gate/up 249 -> 235 us, down 227 -> 203..213, the reduction that reads its
+// results 54 -> 48 (full lines written); the step 525 -> 491 us.  1531 tokens:
+// gate/up 210 -> 207, down 137 -> 132.  256 tokens over 64 experts: unchanged
+// within 1 us (88 and 55).
 #include <type_traits>
 
 #include "sw_device.h"
@@ -29,53 +45,86 @@
 namespace sw {
 namespace {
 
-constexpr int kWv = 8;                 // waves per block
-constexpr int kBlk = 64 * kWv;         // threads per block
-constexpr int kTpw = 2;                // 16-row tiles per wave per unit
-constexpr int kTpu = kWv * kTpw;       // tiles per unit
-constexpr int kNB = 10;                // 16-token column blocks per pass
-constexpr int kNT = 16 * kNB;          // tokens per pass
-constexpr int kPad = 8;                // bf16 padding per staged row
-constexpr int kRowsPad = kNT + 32;     // staged rows: the pass's, then a trash area that
-                                       // takes the idle slots of a partial staging round
+constexpr int kWv = 8;                    // waves per block
+constexpr int kBlk = 64 * kWv;            // threads per block
+constexpr int kTpw = 4;                   // 16-row tiles per wave
+constexpr int kRowGroups = 4;             // waves w % 4: row tiles
+constexpr int kColGroups = kWv / kRowGroups;  // waves w / 4: column blocks
+constexpr int kTpu = kTpw * kRowGroups;   // tiles per unit
+constexpr int kMaxNb = 5;                 // 16-token column blocks of a wave
+constexpr int kNT = 16 * kMaxNb * kColGroups;  // tokens per pass
+constexpr int kFrag = 512;                // 16-bit words of a fragment: 16 rows x 32 columns
+static_assert(kTpu % kWv == 0, "whole rounds of weight loads");
 
-// gate/up: chunk = 2 K steps (64 columns of x), 3 chunks of weights in flight
-constexpr int kGuKs = 2;
-constexpr int kGuKc = 32 * kGuKs;
-// Pipeline depth D: D chunks of weights held in registers per wave and D
-// ring slots of staged activations in LDS, so D - 1 chunks of each are in
-// flight ahead of the one computed.  The code takes 2 or 4; 2 measured
-// faster for both kernels (about 4% for gate/up, 14% for down at the
-// 4096-token prefill shape).
-constexpr int kDepth = 2;
-constexpr int kSegRows = 8;            // staged rows per 1 KiB direct-to-LDS load of a wave
-static_assert(kGuKc * 2 * kSegRows == 1024, "one wave load fills kSegRows rows");
-// down: chunk = 2 K steps (64 columns of h hi and of h lo), 3 in flight;
-// the staged h goes through the same kind of ring as gate/up's x
-constexpr int kDnKs = 2;
-constexpr int kDnKc = 32 * kDnKs;
-static_assert(kDnKc == kGuKc, "one segment geometry for both staged operands");
+// A staged fragment holds 16 rows of 64 bytes (one 1 KiB load of a wave, four
+// consecutive lanes a row); the four 16-byte pieces of a row sit in swizzled
+// places, so that a 16-lane phase of a 128-bit LDS read (rows 0-3 and 12-15 of
+// one piece, rows 4-11 of the next k-group's) hits distinct banks.  The
+// swizzle is its own inverse.
+__device__ __forceinline__ int place(int row, int piece) { return piece ^ (((row >> 3) & 1) * 3); }
 
-// Unit u -> (active slot a, tile group grp); the expert and its pair range,
-// validated against the plan.
-struct Unit {
-  int e, cnt, base, grp;
-  bool ok;
+// One pass of a unit: (expert, 16 row tiles) x (up to kNT of its pairs).
+struct Pass {
+  int e, grp, base, cnt, p0;
+  int nb;  // column blocks a wave computes: the pass's tokens, split over the column groups
 };
 
-__device__ __forceinline__ Unit unit_of(int u, int gpe, const int* active, const int* counts,
-                                        const int* offsets, int m, int n_pairs) {
-  Unit s;
-  const int a = u / gpe;
-  s.grp = u - a * gpe;
-  const int e = active[a];
-  s.ok = e >= 0 && e < m;
-  s.e = s.ok ? e : 0;
-  s.cnt = s.ok ? counts[s.e] : 0;
-  s.base = s.ok ? offsets[s.e] : 0;
-  s.ok = s.ok && s.cnt > 0 && s.base >= 0 && s.cnt <= n_pairs - s.base;
-  return s;
-}
+// The passes of one block, in order.  The plan is read in three steps that
+// the caller spreads over chunks: each is one round trip to memory.
+struct PassWalk {
+  const int *active, *counts, *offsets;
+  int m, n_pairs, n_units, gpe, step;
+  int u;     // unit of `next`
+  Pass next;
+  bool more;  // `next` is a pass of this block
+
+  __device__ __forceinline__ void set_blocks() {
+    const int n = min(kNT, next.cnt - next.p0);
+    next.nb = (n + 16 * kColGroups - 1) / (16 * kColGroups);
+  }
+  // 1: the following pass of the unit, or the next unit's expert
+  __device__ __forceinline__ void expert_of(const Pass& cur, bool first) {
+    next = cur;
+    more = true;
+    if (!first && cur.p0 + kNT < cur.cnt) {
+      next.p0 = cur.p0 + kNT;
+      return;
+    }
+    if (!first) u += step;
+    next.p0 = 0;
+    next.cnt = 0;
+    more = u < n_units;
+    if (!more) return;
+    const int a = u / gpe;
+    next.grp = u - a * gpe;
+    next.e = active[a];
+  }
+  // 2: its pairs
+  __device__ __forceinline__ void pairs_of() {
+    if (!more || next.p0 > 0) return;
+    const bool ok = next.e >= 0 && next.e < m;
+    next.cnt = ok ? counts[next.e] : 0;
+    next.base = ok ? offsets[next.e] : 0;
+  }
+  // 3: checked against the plan's bounds; units without valid pairs are
+  // skipped (here without spreading: a plan of the dispatch has none)
+  __device__ __forceinline__ void check() {
+    if (!more) return;
+    while (next.p0 == 0 &&
+           !(next.cnt > 0 && next.base >= 0 && next.cnt <= n_pairs - next.base)) {
+      u += step;
+      if (u >= n_units) {
+        more = false;
+        return;
+      }
+      const int a = u / gpe;
+      next.grp = u - a * gpe;
+      next.e = active[a];
+      pairs_of();
+    }
+    set_blocks();
+  }
+};
 
 // Slot of block b in each round of gridDim.x units.  Blocks are dispatched
 // round-robin over the eight XCDs (block b runs on XCD b % 8); giving each
@@ -87,450 +136,632 @@ __device__ __forceinline__ int unit_slot() {
   return (g & 7) ? b : (b & 7) * (g >> 3) + (b >> 3);
 }
 
-// Rows of one pass into LDS: the pair id of dispatch slot p0 + i divided by
-// `div` (k: the token), -1 past the expert's count and in the trash rows.
-__device__ __forceinline__ void load_pass_rows(const int* perm, int base, int p0, int cnt,
-                                               int n_pairs, int div, int* rows) {
-  if ((int)threadIdx.x < kRowsPad) {
-    const int slot = p0 + threadIdx.x;
-    const int p = (int)threadIdx.x < kNT && slot < cnt ? perm[base + slot] : -1;
-    rows[threadIdx.x] = (p >= 0 && p < n_pairs) ? p / div : -1;
+// Waits until at most n of this wave's vector-memory operations are
+// outstanding and its LDS accesses are done.  The instruction takes a
+// constant: n is one of a few values, tried in turn.
+template <int N>
+__device__ __forceinline__ void wait_exactly() {
+  static_assert(N >= 0 && N < 64, "six bits of vmcnt");
+  __builtin_amdgcn_s_waitcnt(vmcnt_at_most_lds_done(N));
+}
+
+// n = lo .. lo + kCount - 1 in steps of kStep (uniform; above: as the last).
+template <int kLo, int kStep, int kCount>
+__device__ __forceinline__ void wait_one_of(int n) {
+  if constexpr (kCount == 1) {
+    wait_exactly<kLo>();
+  } else {
+    if (n <= kLo)
+      wait_exactly<kLo>();
+    else
+      wait_one_of<kLo + kStep, kStep, kCount - 1>(n);
   }
 }
 
-// Column blocks computed by a pass of nbn blocks: every MFMA loop of a pass
-// runs over a compile-time count (no per-block branch between an LDS read
-// and its MFMAs); blocks past the pass's tokens multiply zero rows.
+// Pair ids of walk.next's tokens, straight into LDS (one load of a few waves).
+constexpr int kPidWords = (kNT + 63) / 64 * 64;
+__device__ __forceinline__ void load_pids(u32x4 perm, const PassWalk& walk, int wave, int lane,
+                                          int* dst) {
+  if (wave * 64 < kNT) {  // wave-uniform
+    const int i = wave * 64 + lane, s = walk.next.p0 + i;
+    load_lds4(perm,
+              i < kNT && s < walk.next.cnt ? (uint32_t)(walk.next.base + s) * 4u : kOutOfRange,
+              lds_address(dst + wave * 64));
+  }
+}
+
+// This wave's LDS accesses are done; past the barrier so are every wave's.
+__device__ __forceinline__ void pass_barrier() {
+  __builtin_amdgcn_s_waitcnt(vmcnt_at_most_lds_done(63));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");  // (no LDS read moves above it)
+}
+
+__device__ __forceinline__ void landed_barrier() {
+  __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));
+  pass_barrier();
+}
+
+// The chunk's MFMAs, in the K order of every output.
+template <int NB>
+__device__ __forceinline__ void chunk_mfmas(const u32x4 (&a)[kTpw], const u32x4 (&b)[NB],
+                                            f32x4 (&acc)[kTpw][NB]) {
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int t = 0; t < kTpw; ++t) acc[t][nb] = mfma_16x16x32(a[t], b[nb], acc[t][nb]);
+}
+
+// A wave's operands of one MFMA step: 4 row tiles, NB column blocks.
+template <int NB>
+struct Operands {
+  u32x4 a[kTpw], b[NB];
+};
+
+// gate/up's activations of a chunk are 4 loads of 1 KiB for every column block
+// of a wave, dealt out over the 8 waves in rounds; an odd number of blocks leaves
+// half a round, which the other half repeats, so that every wave issues the
+// same number.
+__host__ __device__ constexpr int act_loads(int nb) { return (4 * nb + kWv - 1) / kWv; }
+constexpr int kMaxActLoads = act_loads(kMaxNb);
+__device__ __forceinline__ int act_load(int nb, int wave, int j) {
+  const int f = wave + j * kWv;
+  return f < 4 * nb ? f : f - 4;
+}
+
 template <typename F>
-__device__ __forceinline__ void with_blocks(int nbn, F&& f) {
-  if (nbn <= 4)
-    f(std::integral_constant<int, 4>{});
-  else if (nbn <= 8)
-    f(std::integral_constant<int, 8>{});
-  else
-    f(std::integral_constant<int, kNB>{});
+__device__ __forceinline__ void with_blocks(int nb, F&& f) {
+  switch (nb) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    case 4: f(std::integral_constant<int, 4>{}); break;
+    default: f(std::integral_constant<int, 5>{}); break;
+  }
 }
 
 // ---------------------------------------------------------------------------
 // gate/up + SwiGLU
+//
+// A chunk is 64 columns (two MFMA steps), the ring three slots.  The one
+// barrier of a chunk sits between its two steps: by then every wave has read
+// the chunk's operands, so its slot takes the chunk three ahead, and the next
+// chunk, which has landed, gives its first step's operands during the MFMAs of
+// the second.  (One step a chunk and barrier, in a ring of four: 249 us at 4096
+// tokens.  With the waits for loads chosen inside one loop over the chunks, and
+// the first step's MFMAs waiting for the second's LDS reads too: 265.)  The
+// number of loads a wave issues for a chunk is the same for every wave and a
+// constant of the pass, so the loop over the chunks has one wait and no branch.
 
-// Weight chunk c of the wave's tiles: kGuKs fragments of 1 KiB per tile.
+constexpr int kGuCols = 64, kGuSteps = kGuCols / 32, kGuSlots = 3;
+constexpr int kGuTile = 16 * kGuCols;                       // words of a tile's chunk
+constexpr int kGuX = kTpu * kGuTile;                        // the slot's x rows start here
+constexpr int kGuSlot = kGuX + kNT * kGuCols;               // words
+constexpr int kGuW = kTpu * kGuSteps / kWv;                 // weight loads a wave and chunk
+constexpr int kGuOverlap = 8;  // chunks from which a pass looks up and stages the next one
+static_assert(kWv * 2 * kFrag <= kGuSlot, "a slot holds the waves' result transpositions");
+
 template <bool kTiled>
-__device__ __forceinline__ void gu_issue(__amdgpu_buffer_rsrc_t w, const int (&ib)[kTpw],
-                                         int c, int nchunks, int H, int I, int lane,
-                                         u32x4 (&A)[kTpw][kGuKs]) {
-  const int r = lane & 15, kg = lane >> 4;
-#pragma unroll
-  for (int t = 0; t < kTpw; ++t) {
-    uint32_t row, stride;
-    if (kTiled) {
-      row = (uint32_t)ib[t] * 32u * H + (uint32_t)lane * 16u;
-      stride = 1024u;
-    } else {
-      const int wrow = r < 8 ? ib[t] * 8 + r : I + ib[t] * 8 + (r - 8);
-      row = (uint32_t)wrow * H * 2u + kg * 16u;
-      stride = 64u;
-    }
-    const bool ok = c < nchunks && ib[t] >= 0;
-#pragma unroll
-    for (int s = 0; s < kGuKs; ++s) {
-      const uint32_t off = ok ? row + (uint32_t)(c * kGuKs + s) * stride : kOutOfRange;
-      A[t][s] = kTiled ? buf_ld128_stream(w, off) : buf_ld128(w, off);
-    }
-  }
-}
-
-// x of a pass of NBK column blocks goes straight from memory to LDS
-// (buffer loads with the LDS bit: lane l of a wave writes bytes 16 l .. +15
-// of a 1 KiB segment).  A segment holds kSegRows rows of the chunk's 64
-// columns, unpadded; the 16-byte pieces of row R sit in XOR-swizzled slots,
-// slot = piece ^ x_swizzle(R), so that the MFMA operand reads (16 rows, one
-// piece each, per 16 lanes) hit distinct banks.  Segments run over the
-// pass's rows and then, for a partial last round of the waves, the trash
-// rows.
-__device__ __forceinline__ int x_swizzle(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-
-template <int NBK>
-constexpr int gu_segs() {  // direct-to-LDS loads per wave per chunk
-  constexpr int kSegs = (NBK * 16 / kSegRows + kWv - 1) / kWv;
-  static_assert(kSegs * kWv * kSegRows <= kRowsPad, "trash rows hold the idle segments");
-  return kSegs;
-}
-
-template <bool kTiled, int D, int NBK>
-__device__ __forceinline__ void gu_pass(__amdgpu_buffer_rsrc_t w, __amdgpu_buffer_rsrc_t xr,
-                                        const int (&ib)[kTpw], const int* tok,
-                                        uint16_t* __restrict__ x0, uint16_t* __restrict__ x1,
-                                        uint16_t* __restrict__ x2, uint16_t* __restrict__ x3,
-                                        __amdgpu_buffer_rsrc_t hh, __amdgpu_buffer_rsrc_t hl,
-                                        int p0, int cnt, int H, int I, int nchunks, int lane,
-                                        int wave) {
-  // the ring slots as distinct restrict pointers: the compiler then knows
-  // that the loads into one slot do not write the slot being read, and does
-  // not wait for them before the reads
-  static_assert(D == 2 || D == 4, "two or four ring slots");
-  constexpr int kAhead = D - 1;
-  auto slot = [&](int k) { return k == 0 ? x0 : k == 1 ? x1 : k == 2 ? x2 : x3; };
-  constexpr int kSegs = gu_segs<NBK>();
-  constexpr int kWloads = kTpw * kGuKs;  // weight loads per wave per chunk
-  const int r = lane & 15, kg = lane >> 4;
-  // source byte offset of this lane's piece of each segment in chunk 0; a
-  // row without a pair reads out of range in every chunk (at most H * 2
-  // bytes are added to 2^31, still past the resource)
-  uint32_t soff[kSegs];
-#pragma unroll
-  for (int j = 0; j < kSegs; ++j) {
-    const int row = (wave + j * kWv) * kSegRows + (lane >> 3);
-    const int piece = (lane & 7) ^ x_swizzle(row);
-    const int t = tok[row];
-    soff[j] = t >= 0 ? ((uint32_t)t * H + (uint32_t)piece * 8u) * 2u : kOutOfRange;
-  }
-  auto stage = [&](int c, int k) {  // chunk c into ring slot k = c % D
-    uint16_t* buf = slot(k);
-#pragma unroll
-    for (int j = 0; j < kSegs; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          xr, (__attribute__((address_space(3))) void*)(buf + (wave + j * kWv) * kSegRows * kGuKc),
-          16, soff[j] + (uint32_t)c * kGuKc * 2u, 0, 0, 0);
-  };
-  // this lane's operand slot in a staged row, per K step (row & 15 = r)
-  int bslot[kGuKs];
-#pragma unroll
-  for (int st = 0; st < kGuKs; ++st) bslot[st] = ((st * 4 + kg) ^ x_swizzle(r)) * 8;
-
-  // prologue: x chunks 0 .. D - 2, then weight chunks 0 .. D - 2
-#pragma unroll
-  for (int c = 0; c < kAhead; ++c) stage(c, c);
-  __builtin_amdgcn_sched_barrier(0);  // the load order the waits below count on
-  u32x4 A[D][kTpw][kGuKs];
-#pragma unroll
-  for (int d = 0; d < kAhead; ++d) {  // in chunk order: the waits assume it
-    gu_issue<kTiled>(w, ib, d, nchunks, H, I, lane, A[d]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  f32x4 acc[kTpw][NBK];
-#pragma unroll
-  for (int t = 0; t < kTpw; ++t)
-#pragma unroll
-    for (int nb = 0; nb < NBK; ++nb) acc[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // Each chunk issues x chunk c + D - 1 and weight chunk c + D - 1,
-  // unconditionally (nchunks is a multiple of D; past the end the
-  // loads read out of range or land in ring slots never read again), so the
-  // count of loads issued after x chunk c is known: the wait below lets
-  // exactly those stay outstanding.  The compiler does not track the LDS
-  // writes of these loads, hence the explicit wait and a plain barrier
-  // (a __syncthreads fence would wait for every load, weights included).
-  // (the prologue leaves the same count ahead of chunk 0 as a chunk body
-  // leaves ahead of chunk c + D - 1, and the ring slot of chunk c is d)
-  constexpr int kAfter = (kAhead - 1) * (kSegs + kWloads) + kWloads;
-  for (int c0 = 0; c0 < nchunks; c0 += D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int c = c0 + d;
-      // this wave's part of chunk c landed and its reads of chunk c - 1 are done
-      __builtin_amdgcn_s_waitcnt(vmcnt_at_most_lds_done(kAfter));
-      __builtin_amdgcn_s_barrier();  // so for every wave: chunk c - 1's slot is free
-      stage(c + kAhead, (d + kAhead) % D);  // c0 is a multiple of D
-      __builtin_amdgcn_sched_barrier(0);  // x loads first, then the weights (the count)
-      gu_issue<kTiled>(w, ib, c + kAhead, nchunks, H, I, lane, A[(d + kAhead) % D]);
-      // the loads stay ahead of the chunk's MFMAs (the scheduler would sink
-      // them to their first use to shorten register lifetimes)
-      __builtin_amdgcn_sched_barrier(0);
-      const uint16_t* buf = slot(d);
-#pragma unroll
-      for (int st = 0; st < kGuKs; ++st) {
-#pragma unroll
-        for (int nb = 0; nb < NBK; ++nb) {
-          const u32x4 b =
-              *reinterpret_cast<const u32x4*>(buf + (nb * 16 + r) * kGuKc + bslot[st]);
-#pragma unroll
-          for (int t = 0; t < kTpw; ++t) acc[t][nb] = mfma_16x16x32(A[d][t][st], b, acc[t][nb]);
-        }
-      }
-    }
-  }
-  // the x loads past the last chunk write ring slots that the next pass
-  // stages into: they land before this pass ends
-  __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));
-
-  // SwiGLU of each tile's 8 (gate, up) row pairs, two column blocks (a, b)
-  // at a time so that every lane finishes an output: lanes 0-31 hold a's
-  // gates and lanes 32-63 a's ups (likewise for b); one exchange across the
-  // halves hands lanes 0-31 a's ups and lanes 32-63 b's gates.  The
-  // arithmetic per output is unchanged.
-  static_assert(NBK % 2 == 0, "column blocks in pairs");
-  const int half = lane >> 5, kgx = (lane >> 4) & 1;
-#pragma unroll
-  for (int t = 0; t < kTpw; ++t) {
-#pragma unroll
-    for (int nb = 0; nb < NBK; nb += 2) {
-      f32x4 g4, u4;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float a = acc[t][nb][i], b = acc[t][nb + 1][i];
-        const float y = __shfl_xor(half ? a : b, 32);  // lanes < 32: a's up; else b's gate
-        g4[i] = half ? y : a;
-        u4[i] = half ? b : y;
-      }
-      float hv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) hv[i] = swiglu(g4[i], u4[i]);
-      u32x2 hw, lw;
-      split_bf16x4(hv, hw, lw);
-      const int slot = p0 + (nb + half) * 16 + r;
-      uint32_t off = kOutOfRange;
-      if (ib[t] >= 0 && slot < cnt) off = ((uint32_t)slot * I + (uint32_t)(ib[t] * 8 + kgx * 4)) * 2u;
-      __builtin_amdgcn_raw_buffer_store_b64(hw, hh, off, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b64(lw, hl, off, 0, 0);
-    }
-  }
-}
-
-template <bool kTiled, int D>
 __global__ __launch_bounds__(kBlk, 1) void gate_up_prefill_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w13,
     const int* __restrict__ counts, const int* __restrict__ offsets,
     const int* __restrict__ perm, const int* __restrict__ active,
-    const int* __restrict__ n_active_p, uint16_t* __restrict__ h_hi,
-    uint16_t* __restrict__ h_lo, int H, int I, int m, int k, int n_pairs) {
-  __shared__ __attribute__((aligned(1024))) uint16_t xs0[kRowsPad * kGuKc];
-  __shared__ __attribute__((aligned(1024))) uint16_t xs1[kRowsPad * kGuKc];
-  __shared__ __attribute__((aligned(1024))) uint16_t xs2[kRowsPad * kGuKc];
-  __shared__ __attribute__((aligned(1024))) uint16_t xs3[kRowsPad * kGuKc];
-  __shared__ int tok[kRowsPad];
-  const int n_act = *n_active_p;
+    const int* __restrict__ n_active, uint16_t* __restrict__ h_hi, uint16_t* __restrict__ h_lo,
+    int H, int I, int m, int k, int n_pairs) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kGuSlots * kGuSlot];
+  __shared__ int pids_s[2][kPidWords];  // pair ids of the pass and the next
+  const int n_act = *n_active;
   if (n_act <= 0 || n_act > m) return;
-  const int lane = threadIdx.x & 63;
+  const int lane_id = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int tpe = I / 8;                      // tiles per expert
-  const int gpe = (tpe + kTpu - 1) / kTpu;    // units per expert
-  const int nchunks = H / kGuKc;
-  const auto xr = make_rsrc(x, 2u * (uint32_t)(n_pairs / k) * (uint32_t)H);
+  const int tpe = I / 8;                           // tiles per expert: 8 gate and 8 up rows each
+  const int n = H / kGuCols;                       // chunks, at least 2
+  const uint32_t w_bytes = 4u * (uint32_t)I * (uint32_t)H;
+  const u32x4 x_r = rsrc_words(x, 2u * (uint32_t)(n_pairs / k) * (uint32_t)H);
+  const u32x4 perm_r = rsrc_words(perm, 4u * (uint32_t)n_pairs);
+  PassWalk walk{active, counts, offsets, m, n_pairs, n_act * ((tpe + kTpu - 1) / kTpu),
+                (tpe + kTpu - 1) / kTpu, (int)gridDim.x, unit_slot(), {}, false};
 
-  for (int u = unit_slot(); u < n_act * gpe; u += gridDim.x) {
-    const Unit s = unit_of(u, gpe, active, counts, offsets, m, n_pairs);
-    if (!s.ok) continue;  // block-uniform
-    const auto w = make_rsrc(w13 + (size_t)s.e * 2 * I * H, 4u * (uint32_t)I * (uint32_t)H);
-    const uint32_t hbytes = 2u * (uint32_t)s.cnt * (uint32_t)I;
-    const auto hh = make_rsrc(h_hi + (size_t)s.base * I, hbytes);
-    const auto hl = make_rsrc(h_lo + (size_t)s.base * I, hbytes);
-    int ib[kTpw];
+  // What is staged: the pass's weights, and source offsets at chunk 0 (out of
+  // range stays out of range for every chunk: at most a row is added to 2^31).
+  // Staged rows have 128 bytes, their 16-byte pieces in places row_place;
+  // tiled weights keep their fragments.
+  auto row_place = [](int row, int piece) { return piece ^ (row & 7); };
+  u32x4 w_r;
+  uint32_t w_off[kGuW], x_off[kMaxActLoads];
+  auto stage_from = [&](const Pass& s, const int* pids) {
+    int lane = lane_id;
+    asm volatile("" : "+v"(lane));  // (nothing of this is kept across passes)
+    const int l_row = lane >> 3, l_piece = row_place(l_row, lane & 7);
+    w_r = rsrc_words(w13 + (size_t)s.e * 2 * I * H, w_bytes);
 #pragma unroll
-    for (int t = 0; t < kTpw; ++t) {
-      const int tile = s.grp * kTpu + wave * kTpw + t;
-      ib[t] = tile < tpe ? tile : -1;
+    for (int j = 0; j < kGuW; ++j) {
+      // load f = wave + 8 j: half f % 2 of tile f / 2 -- a fragment, or rows
+      const int f = wave + j * kWv, tile = s.grp * kTpu + f / 2;
+      if (kTiled)
+        w_off[j] = (uint32_t)tile * 32u * (uint32_t)H + (uint32_t)(f % 2) * 1024u +
+                   (uint32_t)lane * 16u;
+      else  // the 8 gate rows, the 8 up rows
+        w_off[j] = ((uint32_t)((f % 2) * I + tile * 8 + l_row) * (uint32_t)H +
+                    (uint32_t)l_piece * 8u) * 2u;
+      if (tile >= tpe) w_off[j] = kOutOfRange;
     }
+#pragma unroll
+    for (int j = 0; j < kMaxActLoads; ++j) {
+      const int row = act_load(s.nb, wave, j) * 8 + l_row, sl = s.p0 + row;
+      const int q = row < kNT ? pids[row] : -1;
+      x_off[j] = row < kNT && sl < s.cnt && q >= 0 && q < n_pairs
+                     ? ((uint32_t)(q / k) * (uint32_t)H + (uint32_t)l_piece * 8u) * 2u
+                     : kOutOfRange;
+    }
+  };
+  const uint32_t ring_at = lds_address(ring);
+  constexpr uint32_t kSlotBytes = kGuSlot * 2;
+  auto next_slot = [](uint32_t q) {
+    return q + kSlotBytes == kGuSlots * kSlotBytes ? 0u : q + kSlotBytes;
+  };
+  // chunk c of a pass with nb column blocks into the slot at byte q
+  auto stage = [&](auto nbc, int c, uint32_t q) {
+    constexpr int NB = decltype(nbc)::value;
+    const uint32_t at = ring_at + q + (uint32_t)wave * 1024u;
+    const uint32_t wc = (uint32_t)c * (kTiled ? 2048u : 128u), xc = (uint32_t)c * 128u;
+    for_each_index<kGuW>([&](auto j) {
+      load_lds16<decltype(j)::value * kWv * 1024, kTiled>(w_r, w_off[decltype(j)::value], wc, at);
+    });
+    // (the last round of an odd number of blocks repeats its first half)
+    for_each_index<act_loads(NB)>([&](auto j) {
+      constexpr int J = decltype(j)::value;
+      constexpr bool kRepeat = (J + 1) * kWv > 4 * NB;
+      const uint32_t back = kRepeat ? (uint32_t)(wave & 4) * 1024u : 0u;
+      load_lds16<kGuX * 2 + J * kWv * 1024>(x_r, x_off[J], xc, at - back);
+    });
+  };
+  auto stage_next = [&](int c, uint32_t q) {
+    with_blocks(walk.next.nb, [&](auto nbc) { stage(nbc, c, q); });
+  };
 
-    for (int p0 = 0; p0 < s.cnt; p0 += kNT) {
-      const int nbn = (min(kNT, s.cnt - p0) + 15) >> 4;
-      __syncthreads();  // the previous pass's readers of tok and xs are done
-      load_pass_rows(perm, s.base, p0, s.cnt, n_pairs, k, tok);
-      __syncthreads();
-      with_blocks(nbn, [&](auto nbk) {
-        gu_pass<kTiled, D, decltype(nbk)::value>(w, xr, ib, tok, xs0, xs1, xs2, xs3, hh, hl, p0,
-                                              s.cnt, H, I, nchunks, lane, wave);
-      });
+  Pass cur{0, 0, 0, 0, 0, 0};
+  int half = 0;        // the pass's half of pids_s
+  uint32_t q = 0;      // slot of the chunk being computed, in bytes
+  int stored = 0;      // result stores of the last pass, by this wave (0: all waited for)
+  const bool overlap = n >= kGuOverlap;
+  // a pass from an empty pipeline: the first one, and every one of a short K
+  auto start = [&](bool first) {
+    walk.expert_of(cur, first);
+    walk.pairs_of();
+    walk.check();
+    if (!walk.more) return;
+    load_pids(perm_r, walk, wave, lane_id, pids_s[half]);
+    landed_barrier();
+    stored = 0;
+    stage_from(walk.next, pids_s[half]);
+    stage_next(0, q);
+    stage_next(1, next_slot(q));
+  };
+  start(true);
+  if (!walk.more) return;
+  cur = walk.next;
+
+  auto run_pass = [&](auto nbc) {
+    constexpr int NB = decltype(nbc)::value;
+    constexpr int kLoads = kGuW + act_loads(NB);  // a wave's loads of a chunk
+    int lane = lane_id;
+    asm volatile("" : "+v"(lane));  // (the addresses of the five widths are not kept)
+    const int r = lane & 15, kg = lane >> 4;
+    f32x4 acc[kTpw][NB];
+#pragma unroll
+    for (int t = 0; t < kTpw; ++t)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int w_at[kGuSteps], x_at[kGuSteps];  // operand places in a slot (bytes), per step
+#pragma unroll
+    for (int st = 0; st < kGuSteps; ++st) {
+      const int pl = row_place(r, st * 4 + kg) * 8;
+      w_at[st] = 2 * ((wave % kRowGroups) * kTpw * kGuTile +
+                      (kTiled ? st * kFrag + lane * 8 : r * kGuCols + pl));
+      x_at[st] = 2 * (kGuX + ((wave / kRowGroups) * NB * 16 + r) * kGuCols + pl);
     }
+    auto read = [&](Operands<NB>& o, uint32_t slot, auto stc) {
+      constexpr int st = decltype(stc)::value;
+      const char* wb = reinterpret_cast<const char*>(ring) + (slot + (uint32_t)w_at[st]);
+      const char* xb = reinterpret_cast<const char*>(ring) + (slot + (uint32_t)x_at[st]);
+#pragma unroll
+      for (int t = 0; t < kTpw; ++t)
+        o.a[t] = *reinterpret_cast<const u32x4*>(wb + t * kGuTile * 2);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        o.b[nb] = *reinterpret_cast<const u32x4*>(xb + nb * 16 * kGuCols * 2);
+      __builtin_amdgcn_sched_barrier(0);  // on their way during the MFMAs that follow
+    };
+    // waits until only one chunk's loads, and the last pass's result stores,
+    // are outstanding
+    auto wait_past_stores = [&]() {
+      wait_one_of<kLoads, 2, kMaxNb + 1>(kLoads + stored);
+    };
+
+    // Chunk 0 landed: after its loads came chunk 1's and the last pass's
+    // stores.  Past the barrier no wave reads the last pass's results from
+    // the slot that chunk 2 takes.
+    wait_past_stores();
+    pass_barrier();
+    if (2 < n) stage(nbc, 2, next_slot(next_slot(q)));
+    Operands<NB> o0, o1;
+    read(o0, q, std::integral_constant<int, 0>{});
+    // One chunk: the MFMAs of its two steps, `between` (the wait for the next
+    // chunk, the barrier after which every wave has this chunk's operands, and
+    // what is staged into its slot) between them.
+    auto chunk = [&](auto last, auto&& between) {
+      constexpr bool kLast = decltype(last)::value;
+      // step 0's operands have arrived (during the previous MFMAs); said here,
+      // so that their MFMAs do not wait for step 1's
+      __builtin_amdgcn_s_waitcnt(vmcnt_at_most_lds_done(63));
+      read(o1, q, std::integral_constant<int, 1>{});
+      chunk_mfmas<NB>(o0.a, o0.b, acc);
+      between();
+      if constexpr (!kLast) {
+        const uint32_t nq = next_slot(q);
+        read(o0, nq, std::integral_constant<int, 0>{});
+        q = nq;
+      }
+      chunk_mfmas<NB>(o1.a, o1.b, acc);
+    };
+    using No = std::false_type;
+    using Yes = std::true_type;
+    if (overlap) {
+      // The next pass is looked up in two steps; its pair ids land before
+      // chunk 4, so before they are used at the earliest (chunk n - 3).  Chunk
+      // c + 1 has landed when only chunk c + 2's loads (for c = 0 also the
+      // stores before them) are outstanding.
+      chunk(No{}, [&]() {
+        wait_past_stores();
+        pass_barrier();
+        walk.expert_of(cur, false);
+        stage(nbc, 3, q);
+      });
+      chunk(No{}, [&]() {
+        wait_exactly<kLoads>();
+        pass_barrier();
+        walk.pairs_of();
+        walk.check();
+        if (walk.more) load_pids(perm_r, walk, wave, lane_id, pids_s[half ^ 1]);
+        stage(nbc, 4, q);
+      });
+      for (int c = 2; c + 3 < n; ++c)
+        chunk(No{}, [&]() {
+          wait_exactly<kLoads>();
+          pass_barrier();
+          stage(nbc, c + 3, q);
+        });
+      chunk(No{}, [&]() {
+        wait_exactly<kLoads>();
+        pass_barrier();
+        if (walk.more) {
+          stage_from(walk.next, pids_s[half ^ 1]);
+          stage_next(0, q);
+        }
+      });
+      chunk(No{}, [&]() {
+        if (walk.more)
+          wait_one_of<kGuW + 1, 1, kMaxActLoads>(kGuW + act_loads(walk.next.nb));
+        else
+          wait_exactly<0>();
+        pass_barrier();
+        if (walk.more) stage_next(1, q);
+      });
+    } else {
+      for (int c = 0; c + 1 < n; ++c)
+        chunk(No{}, [&]() {
+          if (c + 2 < n)
+            wait_exactly<kLoads>();
+          else
+            wait_exactly<0>();
+          pass_barrier();
+          if (c + 3 < n) stage(nbc, c + 3, q);
+        });
+    }
+    // (the last chunk's slot carries the results; the next pass's chunk 2
+    // follows them)
+    chunk(Yes{}, [&]() { pass_barrier(); });
+
+    // SwiGLU of two tiles at a time, so that every lane finishes an output:
+    // lanes 0-31 hold tile a's gates and lanes 32-63 its ups (likewise for
+    // tile b); one exchange across the halves hands lanes 0-31 a's ups and
+    // lanes 32-63 b's gates.  The 32 outputs of a token then pass through the
+    // wave's part of the free slot, so that four consecutive lanes store 64
+    // consecutive bytes of it (a store with a token per lane costs the address
+    // path a cycle a lane).
+    uint16_t* trans = ring + q / 2 + wave * 2 * kFrag;
+    const int tile0 = cur.grp * kTpu + (wave % kRowGroups) * kTpw;
+    const int blk0 = (wave / kRowGroups) * NB;
+    const uint32_t hbytes = 2u * (uint32_t)cur.cnt * (uint32_t)I;
+    const auto hh = make_rsrc(h_hi + (size_t)cur.base * I, hbytes);
+    const auto hl = make_rsrc(h_lo + (size_t)cur.base * I, hbytes);
+    const int up = lane >> 5, kgx = kg & 1;
+    const int l_row = lane >> 2, l_piece = place(l_row, lane & 3);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+      for (int t = 0; t < kTpw; t += 2) {
+        f32x4 g4, u4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float a = acc[t][nb][i], b = acc[t + 1][nb][i];
+          const float z = __shfl_xor(up ? a : b, 32);  // lanes < 32: a's up; else b's gate
+          g4[i] = up ? z : a;
+          u4[i] = up ? b : z;
+        }
+        float hv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hv[i] = swiglu(g4[i], u4[i]);
+        u32x2 hw, lw;
+        split_bf16x4(hv, hw, lw);
+        uint16_t* at = trans + (r * 4 + place(r, t + up)) * 8 + kgx * 4;
+        *reinterpret_cast<u32x2*>(at) = hw;
+        *reinterpret_cast<u32x2*>(at + kFrag) = lw;
+      }
+      const u32x4 vh = *reinterpret_cast<const u32x4*>(trans + lane * 8);
+      const u32x4 vl = *reinterpret_cast<const u32x4*>(trans + kFrag + lane * 8);
+      const int sl = cur.p0 + (blk0 + nb) * 16 + l_row, tile = tile0 + l_piece;
+      const uint32_t off =
+          sl < cur.cnt && tile < tpe ? ((uint32_t)sl * I + (uint32_t)tile * 8u) * 2u : kOutOfRange;
+      __builtin_amdgcn_raw_buffer_store_b128(vh, hh, off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(vl, hl, off, 0, 0);
+    }
+    stored = 2 * NB;
+    q = next_slot(q);
+  };
+  for (;;) {
+    with_blocks(cur.nb, run_pass);
+    if (overlap) {
+      half ^= 1;
+    } else {
+      pass_barrier();  // (every wave is done with the pair ids and the results' slot)
+      start(false);
+    }
+    if (!walk.more) break;
+    cur = walk.next;
   }
+  __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));
 }
 
 // ---------------------------------------------------------------------------
 // down projection
+//
+// A chunk is one MFMA step (32 columns) of the weights and of both h planes,
+// the ring four slots.  A chunk's weight and hi operands are in registers
+// before its turn; the lo plane is read in its turn, during the hi plane's
+// MFMAs (both planes a chunk ahead take more registers than there are).
+
+constexpr int kDnSlots = 4, kDnAhead = kDnSlots - 1;
+constexpr int kDnPlane = kNT * 32;                          // words of a staged plane
+constexpr int kDnSlot = kTpu * kFrag + 2 * kDnPlane;
+constexpr int kDnW = kTpu / kWv;                            // weight loads a wave and chunk
+constexpr int kDnHLoads = (2 * kColGroups * kMaxNb + kWv - 1) / kWv;  // at most, h loads
+
+template <bool kTiled, int NB>
+__device__ __forceinline__ void dn_read(Operands<NB>& o, const uint16_t* buf, int wave, int lane) {
+  const int r = lane & 15, kg = lane >> 4;
+  const int at = (r * 4 + place(r, kg)) * 8;
+  const uint16_t* wf = buf + (wave % kRowGroups) * kTpw * kFrag + (kTiled ? lane * 8 : at);
+  const uint16_t* bf = buf + kTpu * kFrag + (wave / kRowGroups) * NB * kFrag + at;
+#pragma unroll
+  for (int t = 0; t < kTpw; ++t) o.a[t] = *reinterpret_cast<const u32x4*>(wf + t * kFrag);
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) o.b[nb] = *reinterpret_cast<const u32x4*>(bf + nb * kFrag);
+}
+
+template <int NB>
+__device__ __forceinline__ void dn_read_lo(u32x4 (&b)[NB], const uint16_t* buf, int wave,
+                                           int lane) {
+  const int r = lane & 15, kg = lane >> 4;
+  const uint16_t* bf = buf + kTpu * kFrag + kDnPlane + (wave / kRowGroups) * NB * kFrag +
+                       (r * 4 + place(r, kg)) * 8;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) b[nb] = *reinterpret_cast<const u32x4*>(bf + nb * kFrag);
+}
 
 template <bool kTiled>
-__device__ __forceinline__ void dn_issue(__amdgpu_buffer_rsrc_t w, const int (&ob)[kTpw], int c,
-                                         int nchunks, int H, int I, int lane,
-                                         u32x4 (&A)[kTpw][kDnKs]) {
-  const int r = lane & 15, kg = lane >> 4;
-#pragma unroll
-  for (int t = 0; t < kTpw; ++t) {
-    uint32_t row, stride;
-    if (kTiled) {
-      row = (uint32_t)ob[t] * 32u * I + (uint32_t)lane * 16u;
-      stride = 1024u;
-    } else {
-      row = (uint32_t)(ob[t] * 16 + r) * I * 2u + kg * 16u;
-      stride = 64u;
-    }
-    const bool ok = c < nchunks && ob[t] >= 0;
-#pragma unroll
-    for (int s = 0; s < kDnKs; ++s) {
-      const uint32_t off = ok ? row + (uint32_t)(c * kDnKs + s) * stride : kOutOfRange;
-      A[t][s] = kTiled ? buf_ld128_stream(w, off) : buf_ld128(w, off);
-    }
-  }
-}
-
-// h of a pass of NBK column blocks goes straight to LDS like gate/up's x:
-// per ring slot the hi rows, then the lo rows, each kNT rows of the chunk's
-// 64 columns in swizzled 1 KiB segments.  The rows are the expert's dispatch
-// slots base + p0 + row, contiguous, so no pair id is needed to stage them.
-template <int NBK>
-constexpr int dn_segs() {  // direct-to-LDS loads per wave per chunk (both halves)
-  static_assert(2 * NBK * 16 / kSegRows % kWv == 0, "whole rounds of segments");
-  return 2 * NBK * 16 / kSegRows / kWv;
-}
-
-template <bool kTiled, int D, int NBK>
-__device__ __forceinline__ void dn_pass(__amdgpu_buffer_rsrc_t w, __amdgpu_buffer_rsrc_t hhr,
-                                        __amdgpu_buffer_rsrc_t hlr, const int (&ob)[kTpw],
-                                        const int* __restrict__ perm, int n_pairs,
-                                        uint16_t* __restrict__ s0, uint16_t* __restrict__ s1,
-                                        uint16_t* __restrict__ s2, uint16_t* __restrict__ s3,
-                                        __amdgpu_buffer_rsrc_t yr, int base, int p0, int cnt,
-                                        int H, int I, int nchunks, int lane, int wave) {
-  static_assert(D == 2 || D == 4, "two or four ring slots");
-  constexpr int kAhead = D - 1;
-  auto slot = [&](int k) { return k == 0 ? s0 : k == 1 ? s1 : k == 2 ? s2 : s3; };
-  constexpr int kSegs = dn_segs<NBK>(), kSegsHalf = NBK * 16 / kSegRows;
-  constexpr int kWloads = kTpw * kDnKs;
-  const int r = lane & 15, kg = lane >> 4;
-  // the pair (y row) of each of this lane's output columns, for the
-  // epilogue; loaded now, before the staging loads that the waits count
-  int pid[NBK];
-#pragma unroll
-  for (int nb = 0; nb < NBK; ++nb) {
-    const int sl = p0 + nb * 16 + r;
-    const int p = sl < cnt ? perm[base + sl] : -1;
-    pid[nb] = p >= 0 && p < n_pairs ? p : -1;
-  }
-  // source offset of this lane's piece of each segment in chunk 0 (out of
-  // range past the expert's count), its half and its LDS segment
-  uint32_t soff[kSegs];
-#pragma unroll
-  for (int j = 0; j < kSegs; ++j) {
-    const int g = wave + j * kWv;                    // wave-uniform
-    const int gh = g < kSegsHalf ? g : g - kSegsHalf;
-    const int row = gh * kSegRows + (lane >> 3);
-    const int piece = (lane & 7) ^ x_swizzle(row);
-    soff[j] = p0 + row < cnt
-                  ? ((uint32_t)(base + p0 + row) * I + (uint32_t)piece * 8u) * 2u
-                  : kOutOfRange;
-  }
-  auto stage = [&](int c, int k) {  // chunk c into ring slot k = c % D
-    uint16_t* buf = slot(k);
-#pragma unroll
-    for (int j = 0; j < kSegs; ++j) {
-      const int g = wave + j * kWv;
-      const bool lo = g >= kSegsHalf;
-      const int gh = lo ? g - kSegsHalf : g;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          lo ? hlr : hhr,
-          (__attribute__((address_space(3))) void*)(buf + ((lo ? kNT : 0) + gh * kSegRows) * kDnKc),
-          16, soff[j] + (uint32_t)c * kDnKc * 2u, 0, 0, 0);
-    }
-  };
-  int bslot[kDnKs];
-#pragma unroll
-  for (int st = 0; st < kDnKs; ++st) bslot[st] = ((st * 4 + kg) ^ x_swizzle(r)) * 8;
-
-#pragma unroll
-  for (int c = 0; c < kAhead; ++c) stage(c, c);
-  __builtin_amdgcn_sched_barrier(0);  // the load order the waits below count on
-  u32x4 A[D][kTpw][kDnKs];
-#pragma unroll
-  for (int d = 0; d < kAhead; ++d) {  // in chunk order: the waits assume it
-    dn_issue<kTiled>(w, ob, d, nchunks, H, I, lane, A[d]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  f32x4 acc[kTpw][NBK];
-#pragma unroll
-  for (int t = 0; t < kTpw; ++t)
-#pragma unroll
-    for (int nb = 0; nb < NBK; ++nb) acc[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // nchunks is a multiple of D; the waits work as for gate/up
-  constexpr int kAfter = (kAhead - 1) * (kSegs + kWloads) + kWloads;
-  for (int c0 = 0; c0 < nchunks; c0 += D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int c = c0 + d;
-      __builtin_amdgcn_s_waitcnt(vmcnt_at_most_lds_done(kAfter));
-      __builtin_amdgcn_s_barrier();
-      stage(c + kAhead, (d + kAhead) % D);
-      __builtin_amdgcn_sched_barrier(0);
-      dn_issue<kTiled>(w, ob, c + kAhead, nchunks, H, I, lane, A[(d + kAhead) % D]);
-      __builtin_amdgcn_sched_barrier(0);  // loads ahead of the chunk's MFMAs
-      const uint16_t* buf = slot(d);
-#pragma unroll
-      for (int st = 0; st < kDnKs; ++st) {
-#pragma unroll
-        for (int nb = 0; nb < NBK; ++nb) {
-          const uint16_t* row = buf + (nb * 16 + r) * kDnKc + bslot[st];
-          const u32x4 bh = *reinterpret_cast<const u32x4*>(row);
-          const u32x4 bl = *reinterpret_cast<const u32x4*>(row + kNT * kDnKc);
-#pragma unroll
-          for (int t = 0; t < kTpw; ++t) {
-            acc[t][nb] = mfma_16x16x32(A[d][t][st], bh, acc[t][nb]);
-            acc[t][nb] = mfma_16x16x32(A[d][t][st], bl, acc[t][nb]);
-          }
-        }
-      }
-    }
-  }
-  __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));  // the loads past the end landed
-
-  // y rows of the pass's pairs: lane (r, kg) holds output rows
-  // ob * 16 + 4 kg .. + 3 of pair pid[nb]
-#pragma unroll
-  for (int t = 0; t < kTpw; ++t) {
-#pragma unroll
-    for (int nb = 0; nb < NBK; ++nb) {
-      const int o = ob[t] * 16 + kg * 4;
-      uint32_t off = kOutOfRange;
-      if (ob[t] >= 0 && pid[nb] >= 0) off = ((uint32_t)pid[nb] * H + (uint32_t)o) * 4u;
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[t][nb]), yr, off, 0,
-                                             0);
-    }
-  }
-}
-
-template <bool kTiled, int D>
 __global__ __launch_bounds__(kBlk, 1) void down_prefill_kernel(
     const uint16_t* __restrict__ h_hi, const uint16_t* __restrict__ h_lo,
     const uint16_t* __restrict__ w2, const int* __restrict__ counts,
     const int* __restrict__ offsets, const int* __restrict__ perm,
-    const int* __restrict__ active, const int* __restrict__ n_active_p, float* __restrict__ y,
-    int H, int I, int m, int n_pairs) {
-  // the h ring: four slots of hi rows then lo rows
-  __shared__ __attribute__((aligned(1024))) uint16_t hs0[2 * kNT * kDnKc];
-  __shared__ __attribute__((aligned(1024))) uint16_t hs1[2 * kNT * kDnKc];
-  __shared__ __attribute__((aligned(1024))) uint16_t hs2[2 * kNT * kDnKc];
-  __shared__ __attribute__((aligned(1024))) uint16_t hs3[2 * kNT * kDnKc];
-  const int n_act = *n_active_p;
+    const int* __restrict__ active, const int* __restrict__ n_active, float* __restrict__ y, int H,
+    int I, int m, int n_pairs) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kDnSlots * kDnSlot];
+  __shared__ __attribute__((aligned(1024))) uint16_t trans_s[kWv * kFrag];
+  __shared__ int pids_s[2][kPidWords];  // pair ids of the pass and the next
+  const int n_act = *n_active;
   if (n_act <= 0 || n_act > m) return;
-  const int lane = threadIdx.x & 63;
+  const int lane_id = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int tpe = H / 16;
-  const int gpe = (tpe + kTpu - 1) / kTpu;
-  const int nchunks = I / kDnKc;
+  const int tpe = H / 16;                          // tiles per expert: 16 output rows each
+  const int nchunks = I / 32;                      // a multiple of kDnSlots
+  const uint32_t w_bytes = 2u * (uint32_t)H * (uint32_t)I;
+  const uint32_t h_bytes = 2u * (uint32_t)n_pairs * (uint32_t)I;
+  const u32x4 hi_r = rsrc_words(h_hi, h_bytes), lo_r = rsrc_words(h_lo, h_bytes);
+  const u32x4 perm_r = rsrc_words(perm, 4u * (uint32_t)n_pairs);
   const auto yr = make_rsrc(y, 4u * (uint32_t)n_pairs * (uint32_t)H);
-  const uint32_t hbytes = 2u * (uint32_t)n_pairs * (uint32_t)I;
-  const auto hhr = make_rsrc(h_hi, hbytes);
-  const auto hlr = make_rsrc(h_lo, hbytes);
+  uint16_t* trans = trans_s + wave * kFrag;
+  PassWalk walk{active, counts, offsets, m, n_pairs, n_act * ((tpe + kTpu - 1) / kTpu),
+                (tpe + kTpu - 1) / kTpu, (int)gridDim.x, unit_slot(), {}, false};
 
-  for (int u = unit_slot(); u < n_act * gpe; u += gridDim.x) {
-    const Unit s = unit_of(u, gpe, active, counts, offsets, m, n_pairs);
-    if (!s.ok) continue;
-    const auto w = make_rsrc(w2 + (size_t)s.e * H * I, 2u * (uint32_t)H * (uint32_t)I);
-    int ob[kTpw];
+  // what is staged (as for gate/up); the h rows are the expert's dispatch
+  // slots, so they need no pair ids
+  u32x4 w_r;
+  uint32_t w_off[kDnW], b_off[kDnHLoads];
+  int b_loads;  // h fragments of the pass's chunks, over the waves
+  auto stage_from = [&](const Pass& s) {
+    int lane = lane_id;
+    asm volatile("" : "+v"(lane));
+    const int l_row = lane >> 2, l_piece = place(l_row, lane & 3);
+    w_r = rsrc_words(w2 + (size_t)s.e * H * I, w_bytes);
 #pragma unroll
-    for (int t = 0; t < kTpw; ++t) {
-      const int tile = s.grp * kTpu + wave * kTpw + t;
-      ob[t] = tile < tpe ? tile : -1;
+    for (int j = 0; j < kDnW; ++j) {
+      const int tile = s.grp * kTpu + wave + j * kWv;
+      w_off[j] = kTiled ? (uint32_t)tile * 32u * (uint32_t)I + (uint32_t)lane * 16u
+                        : ((uint32_t)(tile * 16 + l_row) * (uint32_t)I + (uint32_t)l_piece * 8u) * 2u;
+      if (tile >= tpe) w_off[j] = kOutOfRange;
+    }
+    b_loads = 2 * kColGroups * s.nb;
+#pragma unroll
+    for (int j = 0; j < kDnHLoads; ++j) {
+      const int f = wave + j * kWv;  // hi blocks, then lo blocks
+      const int b = f >= b_loads / 2 ? f - b_loads / 2 : f;
+      const int sl = s.p0 + b * 16 + l_row;
+      b_off[j] = sl < s.cnt
+                     ? ((uint32_t)(s.base + sl) * (uint32_t)I + (uint32_t)l_piece * 8u) * 2u
+                     : kOutOfRange;
+    }
+  };
+  auto loads_of = [&](int nb) {  // this wave's loads of a chunk
+    const int f = 2 * kColGroups * nb;
+    return kDnW + (f > wave ? (f - wave + kWv - 1) / kWv : 0);
+  };
+  auto slot = [&](int q) { return ring + q * kDnSlot; };
+  const uint32_t ring_at = lds_address(ring);
+  auto stage = [&](int c, int q) {  // chunk c into slot q
+    int w0 = wave;
+    asm volatile("" : "+s"(w0));
+    const uint32_t at = ring_at + (uint32_t)(q * kDnSlot * 2 + w0 * kFrag * 2);
+#pragma unroll
+    for (int j = 0; j < kDnW; ++j)
+      load_lds16<0, kTiled>(w_r, w_off[j], (uint32_t)c * (kTiled ? 1024u : 64u),
+                            at + (uint32_t)(j * kWv * kFrag * 2));
+#pragma unroll
+    for (int j = 0; j < kDnHLoads; ++j) {
+      const int f = w0 + j * kWv;
+      if (f < b_loads) {  // wave-uniform
+        const bool lo = f >= b_loads / 2;
+        const int past = lo ? kNT / 16 - b_loads / 2 : 0;  // the lo plane follows a whole hi plane
+        load_lds16<0>(lo ? lo_r : hi_r, b_off[j], (uint32_t)c * 64u,
+                      at + (uint32_t)((kTpu + past + j * kWv) * kFrag * 2));
+      }
+    }
+  };
+
+  Pass cur{0, 0, 0, 0, 0, 0};
+  walk.expert_of(cur, true);
+  walk.pairs_of();
+  walk.check();
+  if (!walk.more) return;
+  int half = 0;    // the pass's half of pids_s
+  int stored = 0;  // result stores of the last pass, by this wave
+  load_pids(perm_r, walk, wave, lane_id, pids_s[0]);
+  landed_barrier();
+  cur = walk.next;
+  stage_from(cur);
+#pragma unroll
+  for (int c = 0; c < kDnAhead; ++c) stage(c, c);
+
+  auto run_pass = [&](auto nbc) {
+    constexpr int NB = decltype(nbc)::value;
+    int lane = lane_id;
+    asm volatile("" : "+v"(lane));  // (the addresses of the five widths are not kept)
+    const int r = lane & 15, kg = lane >> 4;
+    f32x4 acc[kTpw][NB];
+#pragma unroll
+    for (int t = 0; t < kTpw; ++t)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // this wave's loads of one of the pass's chunks: kLoads, or one more
+    constexpr int kHOfAll = 2 * kColGroups * NB;
+    constexpr int kLoads = kDnW + kHOfAll / kWv;
+    const bool one_more = wave < kHOfAll % kWv;
+    int n_next = 0;
+    // Waits until only the loads of kChunks chunks of this pass, and
+    // (`stores`) the last pass's result stores, are outstanding.
+    auto wait_chunks = [&](auto chunks, bool stores) {
+      constexpr int kChunks = decltype(chunks)::value;
+      if (stores && stored > 0) {
+        if (one_more)
+          wait_one_of<kChunks*(kLoads + 1) + kTpw, kTpw, kMaxNb>(kChunks * (kLoads + 1) + stored);
+        else
+          wait_one_of<kChunks * kLoads + kTpw, kTpw, kMaxNb>(kChunks * kLoads + stored);
+      } else if (one_more) {
+        wait_exactly<kChunks*(kLoads + 1)>();
+      } else {
+        wait_exactly<kChunks * kLoads>();
+      }
+    };
+    Operands<NB> ops[2];
+    // chunk 0 landed: after its loads came those of two more chunks, then the
+    // last pass's stores
+    wait_chunks(std::integral_constant<int, kDnAhead - 1>{}, true);
+    pass_barrier();
+    dn_read<kTiled, NB>(ops[0], slot(0), wave, lane);
+    for (int c0 = 0; c0 < nchunks; c0 += kDnSlots) {
+#pragma unroll
+      for (int d = 0; d < kDnSlots; ++d) {
+        const int c = c0 + d;
+        // Chunk c + 1 landed: after its loads came chunk c + 2's (or the next
+        // pass's first; with no next pass none), and for c < 2 the stores.
+        if (d < 2 || c + kDnAhead <= nchunks)
+          wait_chunks(std::integral_constant<int, kDnAhead - 2>{}, d < kDnAhead - 1 && c0 == 0);
+        else if (c + 1 < nchunks)
+          wait_one_of<0, 1, kDnW + kDnHLoads + 1>(n_next);
+        // past the barrier chunk c - 1's slot is free
+        pass_barrier();
+        // the next pass, in two steps (at once if this one is short)
+        if (c0 == 0) {
+          const bool short_pass = nchunks <= kDnSlots;
+          if (d == 0) {
+            walk.expert_of(cur, false);
+          }
+          if ((d == 0 && short_pass) || (d == 1 && !short_pass)) {
+            walk.pairs_of();
+            walk.check();
+            // (used in the next pass's epilogue, many chunks later)
+            if (walk.more) load_pids(perm_r, walk, wave, lane_id, pids_s[half ^ 1]);
+          }
+        }
+        // the chunk three later, of this pass or the next
+        if (d == kDnSlots - kDnAhead && c + kDnAhead == nchunks && walk.more) {
+          stage_from(walk.next);
+          n_next = loads_of(walk.next.nb);
+        }
+        if (c + kDnAhead < nchunks || walk.more)
+          stage(c + kDnAhead - (c + kDnAhead < nchunks ? 0 : nchunks), (d + kDnAhead) % kDnSlots);
+        u32x4 lo[NB];
+        dn_read_lo<NB>(lo, slot(d), wave, lane);
+        // (past the last chunk: bytes that nothing uses)
+        dn_read<kTiled, NB>(ops[(d + 1) & 1], slot((d + 1) % kDnSlots), wave, lane);
+        __builtin_amdgcn_sched_barrier(0);  // on their way during the MFMAs
+        chunk_mfmas<NB>(ops[d & 1].a, ops[d & 1].b, acc);
+        chunk_mfmas<NB>(ops[d & 1].a, lo, acc);
+      }
     }
 
-    for (int p0 = 0; p0 < s.cnt; p0 += kNT) {
-      const int nbn = (min(kNT, s.cnt - p0) + 15) >> 4;
-      __syncthreads();  // the previous pass's reads of the ring are done
-      with_blocks(nbn, [&](auto nbk) {
-        dn_pass<kTiled, D, decltype(nbk)::value>(w, hhr, hlr, ob, perm, n_pairs, hs0, hs1, hs2,
-                                                 hs3, yr, s.base, p0, s.cnt, H, I, nchunks, lane,
-                                                 wave);
-      });
+    // y: lane (r, kg) holds rows 4 kg .. + 3 of a tile for token r of a column
+    // block; they pass through the wave's own LDS as gate/up's results do
+    const int l_row = lane >> 2, l_piece = place(l_row, lane & 3);
+    const int tile0 = cur.grp * kTpu + (wave % kRowGroups) * kTpw;
+    const int blk0 = (wave / kRowGroups) * NB;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int sl = cur.p0 + (blk0 + nb) * 16 + l_row;
+      const int p = pids_s[half][(blk0 + nb) * 16 + l_row];
+      const bool ok = sl < cur.cnt && p >= 0 && p < n_pairs;
+#pragma unroll
+      for (int t = 0; t < kTpw; ++t) {
+        *reinterpret_cast<u32x4*>(trans + (r * 4 + place(r, kg)) * 8) =
+            __builtin_bit_cast(u32x4, acc[t][nb]);
+        const u32x4 v = *reinterpret_cast<const u32x4*>(trans + lane * 8);
+        const uint32_t off =
+            ok && tile0 + t < tpe
+                ? ((uint32_t)p * (uint32_t)H + (uint32_t)((tile0 + t) * 16 + l_piece * 4)) * 4u
+                : kOutOfRange;
+        __builtin_amdgcn_raw_buffer_store_b128(v, yr, off, 0, 0);
+      }
     }
+    stored = kTpw * NB;
+  };
+  for (;;) {
+    with_blocks(cur.nb, run_pass);
+    if (!walk.more) break;
+    cur = walk.next;
+    half ^= 1;
   }
+  __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));
 }
 
 int prefill_grid() {
@@ -552,8 +783,8 @@ bool prefill_supported(int T, int H, int I, int m, int k) {
   // kept experts 146 -> 100 us a step, gate/up at 5.5 instead of 3.1 TB/s;
   // batch 128 over 64 and batch 256 over 128, 4-6 us faster); at 8 a
   // decode step is faster on the decode kernels.
-  return m >= 16 && (int64_t)T * k >= (int64_t)16 * m && H % (kDepth * kGuKc) == 0 &&
-         I % (kDepth * kDnKc) == 0 &&
+  return m >= 16 && (int64_t)T * k >= (int64_t)16 * m && H % (2 * kGuCols) == 0 &&
+         I % (32 * kDnSlots) == 0 &&
          H <= 32768 && 4 * (int64_t)T * k * H < ((int64_t)1 << 31);
 }
 
@@ -562,10 +793,10 @@ hipError_t launch_gate_up_prefill(const uint16_t* x, int T, const uint16_t* w13,
                                   const int* active, const int* n_active, int H, int I, int m,
                                   int k, uint16_t* h_hi, uint16_t* h_lo, hipStream_t stream) {
   if (tiled)
-    gate_up_prefill_kernel<true, kDepth><<<prefill_grid(), kBlk, 0, stream>>>(
+    gate_up_prefill_kernel<true><<<prefill_grid(), kBlk, 0, stream>>>(
         x, w13, counts, offsets, perm, active, n_active, h_hi, h_lo, H, I, m, k, T * k);
   else
-    gate_up_prefill_kernel<false, kDepth><<<prefill_grid(), kBlk, 0, stream>>>(
+    gate_up_prefill_kernel<false><<<prefill_grid(), kBlk, 0, stream>>>(
         x, w13, counts, offsets, perm, active, n_active, h_hi, h_lo, H, I, m, k, T * k);
   return hipGetLastError();
 }
@@ -576,10 +807,10 @@ hipError_t launch_down_prefill(int T, const uint16_t* w2, bool tiled, const int*
                                const uint16_t* h_hi, const uint16_t* h_lo, float* y,
                                hipStream_t stream) {
   if (tiled)
-    down_prefill_kernel<true, kDepth><<<prefill_grid(), kBlk, 0, stream>>>(
+    down_prefill_kernel<true><<<prefill_grid(), kBlk, 0, stream>>>(
         h_hi, h_lo, w2, counts, offsets, perm, active, n_active, y, H, I, m, T * k);
   else
-    down_prefill_kernel<false, kDepth><<<prefill_grid(), kBlk, 0, stream>>>(
+    down_prefill_kernel<false><<<prefill_grid(), kBlk, 0, stream>>>(
         h_hi, h_lo, w2, counts, offsets, perm, active, n_active, y, H, I, m, T * k);
   return hipGetLastError();
 }

@@ -150,8 +150,8 @@ __global__ __launch_bounds__(64 * kWideWaves) void route_logits_wide_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int r = lane & 15, kg = lane >> 4;
-  const auto w_rsrc = make_rsrc(wr, 4u * (uint32_t)m * (uint32_t)H);
-  const auto x_rsrc = make_rsrc(x, 2u * (uint32_t)T * (uint32_t)H);
+  const u32x4 w_rsrc = rsrc_words(wr, 4u * (uint32_t)m * (uint32_t)H);
+  const u32x4 x_rsrc = rsrc_words(x, 2u * (uint32_t)T * (uint32_t)H);
   const int eg = (wave & 3) * 16, half = wave >> 2;
   const int all = H / kWideKc;
   const int c_lo = ((ks * all) / KS) * (kWideKc / kWideCols);
@@ -179,15 +179,15 @@ __global__ __launch_bounds__(64 * kWideWaves) void route_logits_wide_kernel(
   auto slot = [&](int k) { return k == 0 ? ring0 : k == 1 ? ring1 : k == 2 ? ring2 : ring3; };
   // chunk c into ring slot k = c % kWideSlots
   auto stage = [&](int c, int k) {
-#pragma unroll
-    for (int j = 0; j < kXSegs; ++j)
-      buf_ld128_lds(x_rsrc, x_off[j] + (uint32_t)(c * kWideCols * 2),
-                    slot(k) + (wave + j * kWideWaves) * 512);
-#pragma unroll
-    for (int j = 0; j < kWSegs; ++j)
-      buf_ld128_lds(w_rsrc, w_off[j] + (uint32_t)(c * kWideCols * 4),
-                    slot(k) + kX + (wave + j * kWideWaves) * 512);
-    __builtin_amdgcn_sched_barrier(0);  // ahead of the chunk's arithmetic
+    const uint32_t at = lds_address(slot(k)) + (uint32_t)wave * 1024u;
+    for_each_index<kXSegs>([&](auto j) {
+      load_lds16<decltype(j)::value * kWideWaves * 1024>(x_rsrc, x_off[decltype(j)::value],
+                                                         (uint32_t)(c * kWideCols * 2), at);
+    });
+    for_each_index<kWSegs>([&](auto j) {
+      load_lds16<kX * 2 + decltype(j)::value * kWideWaves * 1024>(
+          w_rsrc, w_off[decltype(j)::value], (uint32_t)(c * kWideCols * 4), at);
+    });
   };
   // this lane's operand places (in 16-bit words), per step
   int b_place[kWideSteps], w_place[kWideSteps][2];
@@ -216,6 +216,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void route_logits_wide_kernel(
       // before are done; then so are every wave's, and that slot is free
       __builtin_amdgcn_s_waitcnt(vmcnt_at_most_lds_done(kAfter));
       __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");  // (no LDS read moves above it)
       stage(c0 + d + kWideAhead, (d + kWideAhead) % kWideSlots);
       const uint16_t* buf = slot(d);
       // every operand read of the chunk goes out before the splits, and the

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace sw {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -53,13 +55,47 @@ __device__ __forceinline__ uint32_t buf_ld32(__amdgpu_buffer_rsrc_t r, uint32_t 
   return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
 }
 
-// 16 bytes a lane straight into LDS: lane l's go to dst + 16 l (dst is
-// wave-uniform; out of range: zeros).  The compiler does not track the LDS
-// write: wait for vmcnt before the bytes are read.
-__device__ __forceinline__ void buf_ld128_lds(__amdgpu_buffer_rsrc_t r, uint32_t off,
-                                              uint16_t* dst) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, off,
-                                           0, 0, 0);
+// 16 bytes a lane straight into LDS: those at byte off + add of r go to LDS
+// byte at + kAt + 16 l for lane l (r, add and at wave-uniform; out of range:
+// zeros).  In assembly, because the compiler would track the builtin's LDS
+// write and wait, before LDS reads that might see it, for a count of loads
+// that holds on every path: with loads issued under conditions that is every
+// load in flight.  The caller waits for vmcnt itself.  No vector register is
+// written, the address is read at issue, and the memory clobber keeps LDS
+// accesses on their side of it.  M0 takes the LDS address; the compiler sets
+// it itself wherever an instruction of its own reads it.
+template <uint32_t kAt, bool kStream = false>  // kStream: read once per call (expert weights)
+__device__ __forceinline__ void load_lds16(u32x4 r, uint32_t off, uint32_t add, uint32_t at) {
+  if constexpr (kStream)
+    asm volatile(
+        "s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen nt lds"
+        :
+        : "v"(off), "s"(r), "s"(add), "s"(at), "n"(kAt)
+        : "memory", "scc");
+  else
+    asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                 :
+                 : "v"(off), "s"(r), "s"(add), "s"(at), "n"(kAt)
+                 : "memory", "scc");
+}
+
+// The same with 4 bytes a lane: lane l's go to at + 4 l.
+__device__ __forceinline__ void load_lds4(u32x4 r, uint32_t off, uint32_t at) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
+               :
+               : "v"(off), "s"(r), "s"(at)
+               : "memory");
+}
+
+// LDS byte address of a __shared__ object.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+
+// The descriptor make_rsrc builds, as the four words load_lds16 takes.
+__device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
+  const uint64_t p = (uint64_t)(uintptr_t)base;
+  return u32x4{(uint32_t)p, (uint32_t)(p >> 32) & 0xffffu, bytes, (uint32_t)kRsrcWord3};
 }
 
 // s_waitcnt immediates (gfx9 encoding): at most n vector-memory operations
@@ -125,6 +161,16 @@ __device__ __forceinline__ void split_bf16x4(const float (&v)[4], u32x2& hi, u32
   const float h0 = __uint_as_float(hi[0] << 16), h1 = __uint_as_float(hi[0] & 0xffff0000u);
   const float h2 = __uint_as_float(hi[1] << 16), h3 = __uint_as_float(hi[1] & 0xffff0000u);
   lo = u32x2{bf16x2_of(v[0] - h0, v[1] - h1), bf16x2_of(v[2] - h2, v[3] - h3)};
+}
+
+// f(std::integral_constant<int, 0>{}), ..., N - 1: a loop whose index is a
+// constant expression.
+template <int N, typename F>
+__device__ __forceinline__ void for_each_index(F&& f) {
+  if constexpr (N > 0) {
+    for_each_index<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
 }
 
 // Monotone map from fp32 to uint32 (a < b  <=>  key(a) < key(b) for

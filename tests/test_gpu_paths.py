@@ -5,8 +5,8 @@ import numpy as np
 import pytest
 
 import oracle
-from parity import GAP_TOL, compare_routing, near_tie_tokens
-from test_gpu_parity import dev, host, small_layer
+from parity import GAP_TOL, compare_out, compare_routing, near_tie_tokens
+from test_gpu_parity import _layer_in_batches, dev, host, small_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -151,3 +151,34 @@ def test_wide_logits_edges(sw, hidden, m, tokens):
     ids, w, gap = sw.sw_moe_route(D["x"], D["wr"], k)
     o_ids, o_w, o_gap, o_z = oracle.route(L["x"], L["wr"], k, want_logits=True)
     compare_routing(host(ids), host(w), o_ids, o_w, o_z, None, k, g_gap=host(gap), o_gap=o_gap)
+
+
+# --------------------------------------------------------------------------
+# the prefill kernels: K of one round of the rings, the last that is too short
+# to look up the next pass (H 384), the first that does (H 512), longer ones;
+# row tiles that end inside a unit (H 128, 384; I 128, 384); more units than
+# blocks (300 experts), experts of several passes, from 1 to 10 column blocks
+
+@pytest.mark.parametrize("tiled", [False, True])
+@pytest.mark.parametrize("hidden,inter,m,k,tokens", [
+    (128, 128, 16, 1, 256), (384, 256, 16, 4, 700), (512, 128, 300, 8, 640),
+    (512, 384, 16, 8, 330), (1152, 256, 24, 4, 450),
+])
+def test_prefill_kernel_edges(sw, hidden, inter, m, k, tokens, tiled):
+    cfg, L, D = small_layer(hidden, m, k, inter, tokens, seed=53)
+    bias = np.linspace(1.0, -1.0, m).astype(np.float32)  # graded loads
+    layout = sw.ROW_MAJOR
+    if tiled:
+        D = dict(D)
+        D["w13"], D["w2"] = sw.sw_moe_pack_experts(D["w13"], D["w2"])
+        layout = sw.TILED
+    d = sw.dims(hidden, inter, m, k)
+    assert sw.sw_moe_forward_kernels(d, tokens, layout) == ("prefill", "prefill")
+    g = sw.moe_layer(D["x"], D["wr"], D["w13"], D["w2"], k, bias=dev(bias), layout=layout)
+    g_ids, g_w = host(g["topk_ids"]), host(g["topk_w"])
+    compare_out(host(g["out"]), oracle.forward(L["x"], L["w13"], L["w2"], g_ids, g_w))
+    # the wave kernels accumulate every output over K in the same order (the
+    # split-K ones, which small batches of the deeper layers take, do not)
+    if sw.sw_moe_forward_kernels(d, 16, layout) == ("wave", "wave"):
+        small = _layer_in_batches(sw, D, k, 16, layout, bias=dev(bias))
+        assert torch.equal(g["out"], small)
