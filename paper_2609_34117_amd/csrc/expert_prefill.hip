@@ -22,7 +22,8 @@
 //     pass are computed, and its results stored, while the first chunks of
 //     the next (its expert, pairs and rows looked up a few chunks earlier)
 //     are already on their way.
-// Each output accumulates over K in the same order as the decode kernels.
+// Each output accumulates over K in the same order as the decode kernels,
+// except where the rows of a row-major w13 are a multiple of 4 KiB apart.
 //
 // What bounds it (4096 tokens, 256 experts, H 2048, I 512, top-8: 137 GFLOP of
 // gate/up products, 137 of down's over two planes, 1.6 and 0.8 GB of weights):
@@ -34,8 +35,9 @@
 // row tiles a wave (an LDS operand fed two MFMAs), each pass began with an
 // empty pipeline and results were stored a token per lane.  Before -> now:
 // gate/up 249 -> 235 us, down 227 -> 203..213, the reduction that reads its
-// results 54 -> 48 (full lines written); the step 525 -> 491 us.  1531 tokens:
-// gate/up 210 -> 207, down 137 -> 132.  256 tokens over 64 experts: unchanged
+// results 54 -> 48 (full lines written); the step 525 -> 491 us.  1531 row-major
+// tokens over 128 experts, I 768: gate/up 210 -> 170, down 137 -> 138 (tiled
+// 148 and 124).  256 tokens over 64 experts: unchanged
 // within 1 us (88 and 55).
 #include <type_traits>
 
@@ -268,12 +270,21 @@ __global__ __launch_bounds__(kBlk, 1) void gate_up_prefill_kernel(
   // tiled weights keep their fragments.
   auto row_place = [](int row, int piece) { return piece ^ (row & 7); };
   u32x4 w_r;
+  // Row-major rows of a multiple of 4 KiB have a column of every row in the
+  // same few memory and L2 channels, and blocks in step read the same column:
+  // there the unit's contraction starts grp / gpe into the row and wraps, so
+  // that the units of an expert read different channels.  (H 2048: 1531 tokens
+  // over 128 experts, I 768, 202 -> 170 us; 4096 over 256, I 512, 294 -> 262.
+  // H 1920 as before 159, against 153 tiled; H 1024 no faster with it.)
+  const bool wrap = !kTiled && H % 2048 == 0;
+  int first = 0;  // the chunk of the row that the pass takes first
   uint32_t w_off[kGuW], x_off[kMaxActLoads];
   auto stage_from = [&](const Pass& s, const int* pids) {
     int lane = lane_id;
     asm volatile("" : "+v"(lane));  // (nothing of this is kept across passes)
     const int l_row = lane >> 3, l_piece = row_place(l_row, lane & 7);
     w_r = rsrc_words(w13 + (size_t)s.e * 2 * I * H, w_bytes);
+    first = wrap ? s.grp * n / walk.gpe : 0;
 #pragma unroll
     for (int j = 0; j < kGuW; ++j) {
       // load f = wave + 8 j: half f % 2 of tile f / 2 -- a fragment, or rows
@@ -304,6 +315,10 @@ __global__ __launch_bounds__(kBlk, 1) void gate_up_prefill_kernel(
   auto stage = [&](auto nbc, int c, uint32_t q) {
     constexpr int NB = decltype(nbc)::value;
     const uint32_t at = ring_at + q + (uint32_t)wave * 1024u;
+    if (!kTiled) {
+      c += first;
+      if (c >= n) c -= n;
+    }
     const uint32_t wc = (uint32_t)c * (kTiled ? 2048u : 128u), xc = (uint32_t)c * 128u;
     for_each_index<kGuW>([&](auto j) {
       load_lds16<decltype(j)::value * kWv * 1024, kTiled>(w_r, w_off[decltype(j)::value], wc, at);
