@@ -2,9 +2,13 @@
 // weights of every distinct expert selected across the batch).
 //
 // Every active expert's bf16 weights are streamed from HBM exactly once per
-// call with 128-bit loads straight into matrix-core operand registers (plain
-// loads: measured faster than non-temporal ones for this 16-row access
-// pattern on MI355X); the
+// call with 128-bit loads into matrix-core operand registers.  The streaming
+// kernels load operands at once (plain loads: measured faster than
+// non-temporal ones for 64 bytes of 16 rows a load); the generic ones, which
+// take the longest rows, load 256-byte runs of 4 rows, non-temporal, and
+// transpose in registers, weights and activations alike (24 tokens, 32 experts
+// of H 4096, I 1536, top-4: gate/up 154 -> 134 us, down 114 -> 109; H 3072,
+// I 1024, 48 experts: gate/up 131 -> 118).  The
 // expert's tokens form the narrow side of a 16x16x32 bf16 MFMA (padded to
 // 16 columns), so decode's handful of tokens per expert costs almost no
 // issue time and there is no cross-lane reduction over the hidden size.
@@ -95,7 +99,8 @@ __global__ __launch_bounds__(256) void gate_up_generic_kernel(
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, kg = lane >> 4;
-  const int wrow = r < 8 ? ib * 8 + r : I + ib * 8 + (r - 8);
+  const int l0 = row_of_load(lane, 0);  // rows l0 .. + 3 are all gate or all up rows
+  const int wrow = l0 < 8 ? ib * 8 + l0 : I + ib * 8 + (l0 - 8);
   const auto w_rsrc = make_rsrc(w13 + (size_t)e * 2 * I * H, 4u * (uint32_t)I * (uint32_t)H);
   const auto x_rsrc = make_rsrc(x, 2u * (uint32_t)T * (uint32_t)H);
   const auto p_rsrc = make_rsrc(perm + base, 4u * (uint32_t)cnt);
@@ -108,8 +113,8 @@ __global__ __launch_bounds__(256) void gate_up_generic_kernel(
   u32x4 A[KS];
   for (int t0 = 0; t0 < cnt; t0 += 16 * kNbGateUp) {
     const int nbn = (min(16 * kNbGateUp, cnt - t0) + 15) >> 4;
-    // byte offset of each N-block's token row for this lane (out of range
-    // for slots past the expert's count)
+    // byte offset of each N-block's token row r (out of range for slots past
+    // the expert's count); load j reads that of lane j of its quad
     uint32_t pv[kNbGateUp], xoff[kNbGateUp];
 #pragma unroll
     for (int nb = 0; nb < kNbGateUp; ++nb) pv[nb] = buf_ld32(p_rsrc, (uint32_t)(t0 + nb * 16 + r) * 4u);
@@ -129,21 +134,27 @@ __global__ __launch_bounds__(256) void gate_up_generic_kernel(
       if (t0 == 0 || nchunks > 1) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-          const int col = (sb + s) * 32 + kg * 8;
-          const bool ok = sb + s < s_hi && col < H;
-          A[s] = buf_ld128(w_rsrc, ok ? a_row + (uint32_t)col * 2u : kOutOfRange);
+          const int col = (sb + (s & ~3)) * 32 + col_of_load(lane);
+          const bool ok = sb + (s & ~3) + step_of_load(lane) < s_hi && col < H;
+          A[s] = buf_ld128_stream(
+              w_rsrc, ok ? a_row + (uint32_t)((s & 3) * H + col) * 2u : kOutOfRange);
         }
+        rows_to_operands(A, lane);
       }
 #pragma unroll
       for (int nb = 0; nb < kNbGateUp; ++nb) {
         if (nb < nbn) {
+          const uint32_t xj[4] = {quad_perm<0x00>(xoff[nb]), quad_perm<0x55>(xoff[nb]),
+                                  quad_perm<0xAA>(xoff[nb]), quad_perm<0xFF>(xoff[nb])};
           u32x4 B[KS];
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
-            const int col = (sb + s) * 32 + kg * 8;
-            const bool ok = sb + s < s_hi && col < H && xoff[nb] != kOutOfRange;
-            B[s] = buf_ld128(x_rsrc, ok ? xoff[nb] + (uint32_t)col * 2u : kOutOfRange);
+            const int col = (sb + (s & ~3)) * 32 + col_of_load(lane);
+            const bool ok = sb + (s & ~3) + step_of_load(lane) < s_hi && col < H &&
+                            xj[s & 3] != kOutOfRange;
+            B[s] = buf_ld128(x_rsrc, ok ? xj[s & 3] + (uint32_t)col * 2u : kOutOfRange);
           }
+          rows_to_operands(B, lane);
 #pragma unroll
           for (int s = 0; s < KS; ++s) acc[nb] = mfma_16x16x32(A[s], B[s], acc[nb]);
         }
@@ -220,29 +231,32 @@ __global__ __launch_bounds__(256) void down_generic_kernel(
       if (t0 == 0 || nchunks > 1) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-          const int row = o0 + mb * 16 + r;
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
-            const int col = (sb + s) * 32 + kg * 8;
-            const bool ok = row < H && sb + s < s_hi && col < I;
-            A[mb][s] = buf_ld128(
+            const int row = o0 + mb * 16 + row_of_load(lane, s & 3);
+            const int col = (sb + (s & ~3)) * 32 + col_of_load(lane);
+            const bool ok = row < H && sb + (s & ~3) + step_of_load(lane) < s_hi && col < I;
+            A[mb][s] = buf_ld128_stream(
                 w_rsrc, ok ? ((uint32_t)row * I + (uint32_t)col) * 2u : kOutOfRange);
           }
+          rows_to_operands(A[mb], lane);
         }
       }
 #pragma unroll
       for (int nb = 0; nb < kNbDown; ++nb) {
         if (nb < nbn) {
-          const int slot = t0 + nb * 16 + r;
           u32x4 bh[KS], bl[KS];
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
-            const int col = (sb + s) * 32 + kg * 8;
-            const bool ok = slot < cnt && sb + s < s_hi && col < I;
+            const int slot = t0 + nb * 16 + row_of_load(lane, s & 3);
+            const int col = (sb + (s & ~3)) * 32 + col_of_load(lane);
+            const bool ok = slot < cnt && sb + (s & ~3) + step_of_load(lane) < s_hi && col < I;
             const uint32_t off = ok ? ((uint32_t)slot * I + (uint32_t)col) * 2u : kOutOfRange;
             bh[s] = buf_ld128(hh_rsrc, off);
             bl[s] = buf_ld128(hl_rsrc, off);
           }
+          rows_to_operands(bh, lane);
+          rows_to_operands(bl, lane);
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb)
 #pragma unroll

@@ -173,6 +173,66 @@ __device__ __forceinline__ void for_each_index(F&& f) {
   }
 }
 
+// MFMA operands from row-major memory.  An operand wants row l % 16 and the
+// 16-byte piece l / 16 of a 64-byte K step in lane l, but loads whose
+// consecutive lanes lie in different rows cost the address path 64 cycles for
+// 1 KiB, against 16 where four consecutive lanes share 64 bytes.  So four K
+// steps are loaded together: lane (g, q, t) = (l / 16, l / 4 % 4, l % 4) reads,
+// with load j, piece t of step g of row 4 q + j (row_of_load, col_of_load:
+// in 16-bit words from the first step's column); load j of every lane then
+// covers 256 bytes of each of 4 rows.  rows_to_operands turns the four
+// registers into the operands of the four steps: a 4 x 4 transposition over
+// registers and lanes of a quad (register t: piece j of row l % 16), and one
+// over registers and 16-lane rows (register s: piece g of step s).
+__device__ __forceinline__ int row_of_load(int lane, int j) { return (lane & 12) + j; }
+__device__ __forceinline__ int step_of_load(int lane) { return lane >> 4; }
+__device__ __forceinline__ int col_of_load(int lane) { return (lane >> 4) * 32 + (lane & 3) * 8; }
+
+template <int kCtrl>  // a quad permutation
+__device__ __forceinline__ uint32_t quad_perm(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, true);
+}
+
+template <int kCtrl>  // off-diagonal halves of a register pair, over lanes that differ in one bit
+__device__ __forceinline__ void swap_in_quad(uint32_t& a, uint32_t& b, bool upper) {
+  const uint32_t pa = quad_perm<kCtrl>(a), pb = quad_perm<kCtrl>(b);
+  a = upper ? pb : a;
+  b = upper ? b : pa;
+}
+
+template <int N>  // a multiple of 4
+__device__ __forceinline__ void rows_to_operands(u32x4 (&v)[N], int lane) {
+  static_assert(N % 4 == 0, "four K steps together");
+  const bool odd = lane & 1, high = lane & 2;
+#pragma unroll
+  for (int s = 0; s < N; s += 4) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      uint32_t r[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = v[s + j][d];
+      swap_in_quad<0xB1>(r[0], r[1], odd);  // lanes 1 0 3 2
+      swap_in_quad<0xB1>(r[2], r[3], odd);
+      swap_in_quad<0x4E>(r[0], r[2], high);  // lanes 2 3 0 1
+      swap_in_quad<0x4E>(r[1], r[3], high);
+#pragma unroll
+      for (int j = 0; j < 4; j += 2) {
+        const auto w = __builtin_amdgcn_permlane16_swap(r[j], r[j + 1], false, false);
+        r[j] = w[0];
+        r[j + 1] = w[1];
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const auto w = __builtin_amdgcn_permlane32_swap(r[j], r[j + 2], false, false);
+        r[j] = w[0];
+        r[j + 2] = w[1];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[s + j][d] = r[j];
+    }
+  }
+}
+
 // Monotone map from fp32 to uint32 (a < b  <=>  key(a) < key(b) for
 // non-NaN values; -0 and +0 share a key).
 __device__ __forceinline__ uint32_t f32_order_key(float f) {

@@ -184,3 +184,28 @@ def test_prefill_kernel_edges(sw, hidden, inter, m, k, tokens, tiled):
     if same_order and sw.sw_moe_forward_kernels(d, 16, layout) == ("wave", "wave"):
         small = _layer_in_batches(sw, D, k, 16, layout, bias=dev(bias))
         assert torch.equal(g["out"], small)
+
+
+# --------------------------------------------------------------------------
+# row-major weights read in runs of rows and transposed into operands: the
+# wave kernels and the generic ones, a contraction that ends inside a group of
+# four steps and inside a step, output rows that end inside a tile, several
+# column blocks and passes; against the oracle, and (wave) the tiled layout's
+# bits
+
+@pytest.mark.parametrize("hidden,inter,m,k,tokens,family", [
+    (32, 64, 8, 1, 5, "wave"), (160, 96, 8, 1, 30, "wave"), (288, 64, 64, 2, 300, "wave"),
+    (2080, 1056, 32, 2, 40, "generic"), (2568, 1544, 16, 2, 70, "generic"),
+    (4096, 1096, 32, 2, 100, "generic"),
+])
+def test_row_major_operand_edges(sw, hidden, inter, m, k, tokens, family):
+    cfg, L, D = small_layer(hidden, m, k, inter, tokens, seed=59)
+    fams = sw.sw_moe_forward_kernels(sw.dims(hidden, inter, m, k), tokens, sw.ROW_MAJOR)
+    assert fams[0] == family
+    g = sw.moe_layer(D["x"], D["wr"], D["w13"], D["w2"], k, layout=sw.ROW_MAJOR)
+    g_ids, g_w = host(g["topk_ids"]), host(g["topk_w"])
+    compare_out(host(g["out"]), oracle.forward(L["x"], L["w13"], L["w2"], g_ids, g_w))
+    if family == "wave":
+        w13, w2 = sw.sw_moe_pack_experts(D["w13"], D["w2"])
+        t = sw.moe_layer(D["x"], D["wr"], w13, w2, k, layout=sw.TILED)
+        assert torch.equal(g["out"], t["out"])
