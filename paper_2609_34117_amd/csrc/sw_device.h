@@ -62,18 +62,24 @@ __device__ __forceinline__ uint32_t buf_ld32(__amdgpu_buffer_rsrc_t r, uint32_t 
 // that holds on every path: with loads issued under conditions that is every
 // load in flight.  The caller waits for vmcnt itself.  No vector register is
 // written, the address is read at issue, and the memory clobber keeps LDS
-// accesses on their side of it.  M0 takes the LDS address; the compiler sets
-// it itself wherever an instruction of its own reads it.
+// accesses on their side of it.  M0 takes the LDS address; it is a register
+// that the compiler reserves and does not take in a clobber list, so nothing
+// else in a kernel that loads so may use it (a CPU test reads the assembly:
+// no instruction of the compiler's own names it).  Five wait states
+// (the M0 write and the s_nop) stand before the load: the compiler, which does
+// not look into the assembly, may have restored a spilled word of r or add with
+// v_readlane right before it, and a vector-memory instruction must not read an
+// SGPR sooner after a vector write (the load needs one after the M0 write too).
 template <uint32_t kAt, bool kStream = false>  // kStream: read once per call (expert weights)
 __device__ __forceinline__ void load_lds16(u32x4 r, uint32_t off, uint32_t add, uint32_t at) {
   if constexpr (kStream)
     asm volatile(
-        "s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen nt lds"
+        "s_add_u32 m0, %3, %4\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen nt lds"
         :
         : "v"(off), "s"(r), "s"(add), "s"(at), "n"(kAt)
         : "memory", "scc");
   else
-    asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+    asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
                  :
                  : "v"(off), "s"(r), "s"(add), "s"(at), "n"(kAt)
                  : "memory", "scc");
@@ -81,7 +87,7 @@ __device__ __forceinline__ void load_lds16(u32x4 r, uint32_t off, uint32_t add, 
 
 // The same with 4 bytes a lane: lane l's go to at + 4 l.
 __device__ __forceinline__ void load_lds4(u32x4 r, uint32_t off, uint32_t at) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tbuffer_load_dword %0, %1, 0 offen lds"
                :
                : "v"(off), "s"(r), "s"(at)
                : "memory");
