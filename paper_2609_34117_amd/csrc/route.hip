@@ -157,7 +157,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void route_logits_wide_kernel(
   const int c_lo = ((ks * all) / KS) * (kWideKc / kWideCols);
   const int n = (((ks + 1) * all) / KS) * (kWideKc / kWideCols) - c_lo;  // chunks, an even number
   // source offsets of this lane's piece of each segment; a row past the batch
-  // or the pool reads out of range in every chunk (at most a row's bytes are
+  // or the pool reads out of range in every chunk (less than a row's bytes are
   // added to 2^31, still past the resource)
   uint32_t x_off[kXSegs], w_off[kWSegs];
 #pragma unroll
@@ -178,7 +178,10 @@ __global__ __launch_bounds__(64 * kWideWaves) void route_logits_wide_kernel(
   }
   auto slot = [&](int k) { return k == 0 ? ring0 : k == 1 ? ring1 : k == 2 ? ring2 : ring3; };
   // chunk c into ring slot k = c % kWideSlots
+  // (past the slice's end its last chunk again: load_lds16's `add` stays below
+  // the resource, which a router of one expert is only a row long)
   auto stage = [&](int c, int k) {
+    c = min(c, n - 1);
     const uint32_t at = lds_address(slot(k)) + (uint32_t)wave * 1024u;
     for_each_index<kXSegs>([&](auto j) {
       load_lds16<decltype(j)::value * kWideWaves * 1024>(x_rsrc, x_off[decltype(j)::value],
@@ -205,8 +208,8 @@ __global__ __launch_bounds__(64 * kWideWaves) void route_logits_wide_kernel(
 #pragma unroll
   for (int c = 0; c < kWideAhead; ++c) stage(c, c);
   // Loads issued after chunk c's when chunk c is about to be read: the next
-  // kWideAhead - 1 chunks'.  Chunks past the slice's end are staged like any
-  // other (into slots never read again), so the count holds to the end.
+  // kWideAhead - 1 chunks'.  Past the slice's end the last chunk is staged like
+  // any other (into slots never read again), so the count holds to the end.
   constexpr int kAfter = (kWideAhead - 1) * (kXSegs + kWSegs);
   for (int c0 = 0; c0 < n; c0 += kWideSlots) {
 #pragma unroll

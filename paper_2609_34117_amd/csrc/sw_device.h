@@ -57,7 +57,9 @@ __device__ __forceinline__ uint32_t buf_ld32(__amdgpu_buffer_rsrc_t r, uint32_t 
 
 // 16 bytes a lane straight into LDS: those at byte off + add of r go to LDS
 // byte at + kAt + 16 l for lane l (r, add and at wave-uniform; out of range:
-// zeros).  In assembly, because the compiler would track the builtin's LDS
+// zeros).  `add` must be less than r's size: the range check compares off with
+// what add leaves of it, and a difference below zero need not be out of range
+// for any off.  In assembly, because the compiler would track the builtin's LDS
 // write and wait, before LDS reads that might see it, for a count of loads
 // that holds on every path: with loads issued under conditions that is every
 // load in flight.  The caller waits for vmcnt itself.  No vector register is

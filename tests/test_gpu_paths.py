@@ -140,13 +140,14 @@ def test_dispatch_plan_edges(sw, m, pairs, spread):
 # --------------------------------------------------------------------------
 # prefill-sized router logits: token tiles and expert tiles that end inside a
 # block, experts that are not a multiple of four (scalar stores), one to three
-# slices of H, a slice of two chunks and one that ends in the middle of the ring
+# slices of H, a slice of two chunks and one that ends in the middle of the ring;
+# one expert, whose row the loads past the end of the slice must not leave
 
-@pytest.mark.parametrize("hidden,m,tokens", [
-    (128, 1000, 261), (256, 129, 1900), (1152, 64, 4100), (3072, 250, 1025),
+@pytest.mark.parametrize("hidden,m,tokens,k", [
+    (128, 1000, 261, 4), (256, 129, 1900, 4), (1152, 64, 4100, 4), (3072, 250, 1025, 4),
+    (128, 1, 16400, 1), (384, 2, 16400, 2),
 ])
-def test_wide_logits_edges(sw, hidden, m, tokens):
-    k = 4
+def test_wide_logits_edges(sw, hidden, m, tokens, k):
     cfg, L, D = small_layer(hidden, m, k, 32, tokens, seed=47)
     ids, w, gap = sw.sw_moe_route(D["x"], D["wr"], k)
     o_ids, o_w, o_gap, o_z = oracle.route(L["x"], L["wr"], k, want_logits=True)
