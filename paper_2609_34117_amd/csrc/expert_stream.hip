@@ -389,38 +389,36 @@ struct GuWave {
 };
 
 // Weight chunk q (tile j = q / cpt of this wave, chunk c) of the segment.
-// Row-major: whole 256-byte runs of rows, which rows_to_operands turns into
-// operands when the chunk is computed; tiled: the tile's fragments are
-// contiguous, so the wave reads 1 KiB per load.  Both non-temporal (read
-// once).  A row-major load that is its own operand, 64 bytes of 16 rows, costs
-// the address path four times as much and reads half lines, which must not be
-// non-temporal: 37 tokens over 128 of 256 experts 94 -> 87 us (tiled: 82), 256
-// skewed tokens over 256 214 -> 196, 64 over 64 of I 768 80 -> 73.  (The down
-// projection, two chunks a tile, lost 4 to 10 us by it and reads operands.)
-// Chunks of tiles this wave does not have read out of range.
+// Row-major: lane (r, kg) reads 16 B of weight row r at 64-byte K steps.
+// Tiled: the tile's fragments are contiguous, so the wave reads 1 KiB per
+// load (non-temporal: read once).  Chunks of tiles this wave does not have
+// read out of range.
+// (Row-major in 256-byte runs of 4 rows, transposed into operands in registers
+// as the generic kernels do, saves address cycles but puts 160 vector
+// instructions before a chunk's first MFMA.  Over H 512 to 2048, 60 to 256
+// experts of I 512 to 1024 and 4 to 300 tokens it took 0.93 to 1.39 times as
+// long: 94 to 87 us at 37 tokens over 128 of 256 experts, H 2048, but 4
+// tokens over 128 experts of I 768 went from 31.6 to 39.4 us at H 1536 and from
+// 37.8 to 51.1 at H 1920, and all sizes of H 2016 lost 2 to 39%.)
 template <bool kTiled>
 __device__ __forceinline__ void gu_issue(const GuWave& g, int j, int c, u32x4 (&A)[kKC]) {
   const int tile = g.seg_lo + g.wave + j * kWv;
   const int ib = tile - g.a * g.tpe;
-  const bool live = tile < g.seg_hi;
-  if constexpr (kTiled) {
-    const uint32_t row = (uint32_t)ib * 32u * g.H + (uint32_t)g.lane * 16u;
-#pragma unroll
-    for (int s = 0; s < kKC; ++s) {
-      const int step = c * kKC + s;
-      const uint32_t off = (live && step < g.nsteps) ? row + (uint32_t)step * 1024u : kOutOfRange;
-      A[s] = buf_ld128_stream(g.w, off);
-    }
+  uint32_t row, stride;
+  if (kTiled) {
+    row = (uint32_t)ib * 32u * g.H + (uint32_t)g.lane * 16u;
+    stride = 1024u;
   } else {
-    const int r0 = row_of_load(g.lane, 0);  // rows r0 .. + 3 are all gate or all up rows
-    const uint32_t wrow = r0 < 8 ? ib * 8 + r0 : g.I + ib * 8 + (r0 - 8);
-    const uint32_t at = (wrow * g.H + c * kChunkCols + col_of_load(g.lane)) * 2u;
+    const int wrow = g.r < 8 ? ib * 8 + g.r : g.I + ib * 8 + (g.r - 8);
+    row = (uint32_t)wrow * g.H * 2u + g.kg * 16u;
+    stride = 64u;
+  }
+  const bool live = tile < g.seg_hi;
 #pragma unroll
-    for (int s = 0; s < kKC; ++s) {
-      const bool ok = live && c * kKC + (s & ~3) + step_of_load(g.lane) < g.nsteps;
-      const uint32_t off = at + (uint32_t)((s & 3) * g.H + (s & ~3) * 32) * 2u;
-      A[s] = buf_ld128_stream(g.w, ok ? off : kOutOfRange);
-    }
+  for (int s = 0; s < kKC; ++s) {
+    const int step = c * kKC + s;
+    const uint32_t off = (live && step < g.nsteps) ? row + (uint32_t)step * stride : kOutOfRange;
+    A[s] = kTiled ? buf_ld128_stream(g.w, off) : buf_ld128(g.w, off);
   }
 }
 
@@ -428,10 +426,9 @@ __device__ __forceinline__ void gu_issue(const GuWave& g, int j, int c, u32x4 (&
 // tile's last chunk the SwiGLU epilogue.  The NB pairs of h stores are
 // issued on every chunk (out of range unless they hold a result), so every
 // chunk issues the same memory operations.
-template <bool kTiled, int NB>
-__device__ __forceinline__ void gu_compute(const GuWave& g, const ChunkPos& at, u32x4 (&A)[kKC],
-                                           f32x4 (&acc)[NB]) {
-  if constexpr (!kTiled) rows_to_operands(A, g.lane);
+template <int NB>
+__device__ __forceinline__ void gu_compute(const GuWave& g, const ChunkPos& at,
+                                           const u32x4 (&A)[kKC], f32x4 (&acc)[NB]) {
   const int j = at.j, c = at.c;
   const int tile = g.seg_lo + g.wave + j * kWv;
   const bool have = tile < g.seg_hi;  // false: no tile of this wave in the group
@@ -538,7 +535,7 @@ __device__ __forceinline__ void gu_run(const GuWave& g, u32x4 (&A)[D][kKC], int 
       }
       gu_issue<kTiled>(g, ahead.j, ahead.c, A[(d + D - 1) % D]);
       if (first && !g.dbl) slice_barrier_after<kKC>();
-      if (d == 0 || qd < Q) gu_compute<kTiled, NB>(g, at, A[d], acc);
+      if (d == 0 || qd < Q) gu_compute<NB>(g, at, A[d], acc);
       at.next(g.cpt, g.cps);
       ahead.next(g.cpt, g.cps);
     }

@@ -188,16 +188,16 @@ def test_prefill_kernel_edges(sw, hidden, inter, m, k, tokens, tiled):
 
 
 # --------------------------------------------------------------------------
-# row-major weights read in runs of rows and transposed into operands: the
-# wave kernels and the generic ones, a contraction that ends inside a group of
-# four steps and inside a step, output rows that end inside a tile, several
-# column blocks and passes; against the oracle, and (wave) the tiled layout's
-# bits
+# row-major weights, read as operands (the wave kernels) or in runs of rows that
+# are transposed into operands (the generic ones): a contraction that ends
+# inside a group of four steps and inside a step, output rows that end inside a
+# tile, several column blocks and passes; against the oracle, and (wave) the
+# tiled layout's bits
 
 @pytest.mark.parametrize("hidden,inter,m,k,tokens,family", [
     (32, 64, 8, 1, 5, "wave"), (160, 96, 8, 1, 30, "wave"), (288, 64, 64, 2, 300, "wave"),
     (2080, 1056, 32, 2, 40, "generic"), (2568, 1544, 16, 2, 70, "generic"),
-    (4096, 1096, 32, 2, 100, "generic"),
+    (4096, 1096, 32, 2, 100, "generic"), (2112, 1088, 16, 2, 70, "generic"),
 ])
 def test_row_major_operand_edges(sw, hidden, inter, m, k, tokens, family):
     cfg, L, D = small_layer(hidden, m, k, inter, tokens, seed=59)
