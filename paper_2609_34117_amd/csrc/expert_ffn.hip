@@ -8,7 +8,12 @@
 // take the longest rows, load 256-byte runs of 4 rows, non-temporal, and
 // transpose in registers, weights and activations alike (24 tokens, 32 experts
 // of H 4096, I 1536, top-4: gate/up 154 -> 134 us, down 114 -> 109; H 3072,
-// I 1024, 48 experts: gate/up 131 -> 118).  The
+// I 1024, 48 experts: gate/up 131 -> 118; also where an
+// expert's tokens take several passes: 8 experts of H 4096, I 3584, 400 tokens,
+// top-2, two passes, gate/up 475 -> 314), unless rows are not whole 128-byte lines: a run
+// then ends inside a line that the next run fetches again (H 2568, I 1544, 16
+// experts, 24 tokens, top-4: gate/up 69 us by operands, 74 by runs, down 40 and
+// 43; I 1096, H 4096, 400 tokens over 32 experts: down 242 and 279).  The
 // expert's tokens form the narrow side of a 16x16x32 bf16 MFMA (padded to
 // 16 columns), so decode's handful of tokens per expert costs almost no
 // issue time and there is no cross-lane reduction over the hidden size.
@@ -32,6 +37,7 @@ namespace {
 
 constexpr int kNbGateUp = 4;  // 16-token column blocks per pass of gate_up (64 tokens)
 constexpr int kNbDown = 2;    // ... of down (32 tokens)
+constexpr int kLineCols = 64;  // bf16 values of a 128-byte line
 
 struct ForwardWs {
   uint16_t* h_hi;
@@ -75,13 +81,38 @@ __device__ __forceinline__ bool tile_expert(int tile, int tpe, const int* active
   return true;
 }
 
+// Row, K step and column (from the first of a chunk's steps) that this lane
+// reads with load s of an operand's chunk: in runs of rows, for
+// rows_to_operands, or as the operand itself.
+template <bool kRuns>
+__device__ __forceinline__ int load_row(int lane, int s) {
+  return kRuns ? row_of_load(lane, s & 3) : lane & 15;
+}
+template <bool kRuns>
+__device__ __forceinline__ int load_step(int lane, int s) {
+  return kRuns ? (s & ~3) + step_of_load(lane) : s;
+}
+template <bool kRuns>
+__device__ __forceinline__ int load_col(int lane, int s) {
+  return kRuns ? (s & ~3) * 32 + col_of_load(lane) : s * 32 + (lane >> 4) * 8;
+}
+template <bool kRuns>
+__device__ __forceinline__ u32x4 load_weights(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  return kRuns ? buf_ld128_stream(r, off) : buf_ld128(r, off);
+}
+template <bool kRuns, int N>
+__device__ __forceinline__ void to_operands(u32x4 (&v)[N], int lane) {
+  if constexpr (kRuns) rows_to_operands(v, lane);
+}
+
 // K range of wave w when `nsteps` 32-wide K steps are split four ways.
 __device__ __forceinline__ void wave_ksteps(int nsteps, int wave, int* lo, int* hi) {
   *lo = (wave * nsteps) >> 2;
   *hi = ((wave + 1) * nsteps) >> 2;
 }
 
-template <int KS>
+// kRuns: rows are whole 128-byte lines (H a multiple of 64), and are read in runs.
+template <int KS, bool kRuns>
 __global__ __launch_bounds__(256) void gate_up_generic_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w13,
     const int* __restrict__ counts, const int* __restrict__ offsets,
@@ -99,7 +130,7 @@ __global__ __launch_bounds__(256) void gate_up_generic_kernel(
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, kg = lane >> 4;
-  const int l0 = row_of_load(lane, 0);  // rows l0 .. + 3 are all gate or all up rows
+  const int l0 = load_row<kRuns>(lane, 0);  // the four rows of runs are all gate or all up rows
   const int wrow = l0 < 8 ? ib * 8 + l0 : I + ib * 8 + (l0 - 8);
   const auto w_rsrc = make_rsrc(w13 + (size_t)e * 2 * I * H, 4u * (uint32_t)I * (uint32_t)H);
   const auto x_rsrc = make_rsrc(x, 2u * (uint32_t)T * (uint32_t)H);
@@ -114,7 +145,7 @@ __global__ __launch_bounds__(256) void gate_up_generic_kernel(
   for (int t0 = 0; t0 < cnt; t0 += 16 * kNbGateUp) {
     const int nbn = (min(16 * kNbGateUp, cnt - t0) + 15) >> 4;
     // byte offset of each N-block's token row r (out of range for slots past
-    // the expert's count); load j reads that of lane j of its quad
+    // the expert's count); in runs, load j reads that of lane j of its quad
     uint32_t pv[kNbGateUp], xoff[kNbGateUp];
 #pragma unroll
     for (int nb = 0; nb < kNbGateUp; ++nb) pv[nb] = buf_ld32(p_rsrc, (uint32_t)(t0 + nb * 16 + r) * 4u);
@@ -134,27 +165,33 @@ __global__ __launch_bounds__(256) void gate_up_generic_kernel(
       if (t0 == 0 || nchunks > 1) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-          const int col = (sb + (s & ~3)) * 32 + col_of_load(lane);
-          const bool ok = sb + (s & ~3) + step_of_load(lane) < s_hi && col < H;
-          A[s] = buf_ld128_stream(
-              w_rsrc, ok ? a_row + (uint32_t)((s & 3) * H + col) * 2u : kOutOfRange);
+          const int col = sb * 32 + load_col<kRuns>(lane, s);
+          const bool ok = sb + load_step<kRuns>(lane, s) < s_hi && col < H;
+          const uint32_t row = kRuns ? (uint32_t)(s & 3) * (uint32_t)H : 0u;
+          A[s] = load_weights<kRuns>(w_rsrc,
+                                     ok ? a_row + (row + (uint32_t)col) * 2u : kOutOfRange);
         }
-        rows_to_operands(A, lane);
+        to_operands<kRuns>(A, lane);
       }
 #pragma unroll
       for (int nb = 0; nb < kNbGateUp; ++nb) {
         if (nb < nbn) {
-          const uint32_t xj[4] = {quad_perm<0x00>(xoff[nb]), quad_perm<0x55>(xoff[nb]),
-                                  quad_perm<0xAA>(xoff[nb]), quad_perm<0xFF>(xoff[nb])};
+          uint32_t xj[4] = {xoff[nb], xoff[nb], xoff[nb], xoff[nb]};
+          if constexpr (kRuns) {
+            xj[0] = quad_perm<0x00>(xoff[nb]);
+            xj[1] = quad_perm<0x55>(xoff[nb]);
+            xj[2] = quad_perm<0xAA>(xoff[nb]);
+            xj[3] = quad_perm<0xFF>(xoff[nb]);
+          }
           u32x4 B[KS];
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
-            const int col = (sb + (s & ~3)) * 32 + col_of_load(lane);
-            const bool ok = sb + (s & ~3) + step_of_load(lane) < s_hi && col < H &&
+            const int col = sb * 32 + load_col<kRuns>(lane, s);
+            const bool ok = sb + load_step<kRuns>(lane, s) < s_hi && col < H &&
                             xj[s & 3] != kOutOfRange;
             B[s] = buf_ld128(x_rsrc, ok ? xj[s & 3] + (uint32_t)col * 2u : kOutOfRange);
           }
-          rows_to_operands(B, lane);
+          to_operands<kRuns>(B, lane);
 #pragma unroll
           for (int s = 0; s < KS; ++s) acc[nb] = mfma_16x16x32(A[s], B[s], acc[nb]);
         }
@@ -190,7 +227,8 @@ __global__ __launch_bounds__(256) void gate_up_generic_kernel(
   }
 }
 
-template <int KS, int MB>
+// kRuns: as gate_up_generic_kernel's, of w2's and h's rows (I a multiple of 64).
+template <int KS, int MB, bool kRuns>
 __global__ __launch_bounds__(256) void down_generic_kernel(
     const uint16_t* __restrict__ h_hi, const uint16_t* __restrict__ h_lo,
     const uint16_t* __restrict__ w2, const int* __restrict__ counts,
@@ -233,13 +271,13 @@ __global__ __launch_bounds__(256) void down_generic_kernel(
         for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
-            const int row = o0 + mb * 16 + row_of_load(lane, s & 3);
-            const int col = (sb + (s & ~3)) * 32 + col_of_load(lane);
-            const bool ok = row < H && sb + (s & ~3) + step_of_load(lane) < s_hi && col < I;
-            A[mb][s] = buf_ld128_stream(
+            const int row = o0 + mb * 16 + load_row<kRuns>(lane, s);
+            const int col = sb * 32 + load_col<kRuns>(lane, s);
+            const bool ok = row < H && sb + load_step<kRuns>(lane, s) < s_hi && col < I;
+            A[mb][s] = load_weights<kRuns>(
                 w_rsrc, ok ? ((uint32_t)row * I + (uint32_t)col) * 2u : kOutOfRange);
           }
-          rows_to_operands(A[mb], lane);
+          to_operands<kRuns>(A[mb], lane);
         }
       }
 #pragma unroll
@@ -248,15 +286,15 @@ __global__ __launch_bounds__(256) void down_generic_kernel(
           u32x4 bh[KS], bl[KS];
 #pragma unroll
           for (int s = 0; s < KS; ++s) {
-            const int slot = t0 + nb * 16 + row_of_load(lane, s & 3);
-            const int col = (sb + (s & ~3)) * 32 + col_of_load(lane);
-            const bool ok = slot < cnt && sb + (s & ~3) + step_of_load(lane) < s_hi && col < I;
+            const int slot = t0 + nb * 16 + load_row<kRuns>(lane, s);
+            const int col = sb * 32 + load_col<kRuns>(lane, s);
+            const bool ok = slot < cnt && sb + load_step<kRuns>(lane, s) < s_hi && col < I;
             const uint32_t off = ok ? ((uint32_t)slot * I + (uint32_t)col) * 2u : kOutOfRange;
             bh[s] = buf_ld128(hh_rsrc, off);
             bl[s] = buf_ld128(hl_rsrc, off);
           }
-          rows_to_operands(bh, lane);
-          rows_to_operands(bl, lane);
+          to_operands<kRuns>(bh, lane);
+          to_operands<kRuns>(bl, lane);
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -838,8 +876,10 @@ hipError_t launch_gate_up(const uint16_t* x, int T, const uint16_t* w13, bool ti
                                                           n_active, ws.h_hi, ws.h_lo, H, I, m, k,
                                                           T * k, T);
   } else {
-    gate_up_generic_kernel<16><<<round8(tiles), 256, 0, stream>>>(
-        x, w13, counts, offsets, perm, active, n_active, ws.h_hi, ws.h_lo, H, I, m, k, T * k, T);
+    const auto kernel = H % kLineCols == 0 ? gate_up_generic_kernel<16, true>
+                                           : gate_up_generic_kernel<16, false>;
+    kernel<<<round8(tiles), 256, 0, stream>>>(x, w13, counts, offsets, perm, active, n_active,
+                                              ws.h_hi, ws.h_lo, H, I, m, k, T * k, T);
   }
   return hipGetLastError();
 }
@@ -891,9 +931,12 @@ hipError_t launch_down(int T, const uint16_t* w2, bool tiled, const int* counts,
     launch_down_t<6, 2>(ws, w2, counts, offsets, perm, active, n_active, H, I, m, T * k, stream);
   else if (per_wave <= 8)
     launch_down_t<8, 2>(ws, w2, counts, offsets, perm, active, n_active, H, I, m, T * k, stream);
-  else
-    down_generic_kernel<16, 1><<<round8((long)m * ((H + 15) / 16)), 256, 0, stream>>>(
+  else {
+    const auto kernel = I % kLineCols == 0 ? down_generic_kernel<16, 1, true>
+                                           : down_generic_kernel<16, 1, false>;
+    kernel<<<round8((long)m * ((H + 15) / 16)), 256, 0, stream>>>(
         ws.h_hi, ws.h_lo, w2, counts, offsets, perm, active, n_active, ws.y, H, I, m, T * k);
+  }
   return hipGetLastError();
 }
 
