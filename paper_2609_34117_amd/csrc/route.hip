@@ -740,18 +740,18 @@ __global__ __launch_bounds__(64 * kMassWaves) void mass_partial_kernel(
   }
 }
 
-// Adds the partial rows to the masses: blockIdx.y 0 the softmax mass, 1 the
-// top-k mass.  Thread (r, lane) sums rows r, r + kMassSumRows, ... of expert
+// Adds the partial rows to the masses: first + blockIdx.y 0 the softmax mass, 1
+// the top-k mass.  Thread (r, lane) sums rows r, r + kMassSumRows, ... of expert
 // blockIdx.x * 64 + lane; the row groups are then added in order.  The top-k
 // mass is left alone when fewer than k experts are eligible (every token's
 // selection then lacks a slot).
 __global__ __launch_bounds__(64 * kMassSumRows) void mass_sum_kernel(
     const float* __restrict__ rows, int n_rows, const uint8_t* __restrict__ keep_mask, int m,
-    int k, float* __restrict__ mass_softmax, float* __restrict__ mass_topk) {
+    int k, int first, float* mass_softmax, float* mass_topk) {
   __shared__ float red[kMassSumRows][64];
   const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
-  const int e = blockIdx.x * 64 + lane;
-  float* mass = blockIdx.y == 0 ? mass_softmax : mass_topk;
+  const int e = blockIdx.x * 64 + lane, which = first + (int)blockIdx.y;
+  float* mass = which == 0 ? mass_softmax : mass_topk;
   if (mass == nullptr) return;  // block-uniform
   int missing = 0;              // pruned experts (of those this thread counts)
   if (keep_mask != nullptr)
@@ -759,11 +759,11 @@ __global__ __launch_bounds__(64 * kMassSumRows) void mass_sum_kernel(
   float v = 0.f;
   if (e < m)
     for (int i = r; i < n_rows; i += kMassSumRows)
-      v += rows[(size_t)i * 2 * m + (size_t)blockIdx.y * m + e];
+      v += rows[(size_t)i * 2 * m + (size_t)which * m + e];
   red[r][lane] = v;
   // m <= 64 * kMassSumRows: a thread counts at most one expert
   const int eligible = m - __syncthreads_count(missing);
-  if (r != 0 || e >= m || (blockIdx.y == 1 && eligible < k)) return;
+  if (r != 0 || e >= m || (which == 1 && eligible < k)) return;
   float s = red[0][lane];
 #pragma unroll
   for (int u = 1; u < kMassSumRows; ++u) s += red[u][lane];
@@ -815,8 +815,12 @@ hipError_t launch_routing_mass(const uint16_t* x, int T, const float* wr, const 
 #undef SW_MP
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  mass_sum_kernel<<<dim3((m + 63) / 64, 2), 64 * kMassSumRows, 0, stream>>>(
-      rows, n_rows, keep_mask, m, k, mass_softmax, mass_topk);
+  // one launch for both masses, unless they are the same array: a block adds to
+  // it what it read
+  const int both = mass_softmax == mass_topk ? 1 : 2;
+  for (int first = 0; first < 2; first += both)
+    mass_sum_kernel<<<dim3((m + 63) / 64, both), 64 * kMassSumRows, 0, stream>>>(
+        rows, n_rows, keep_mask, m, k, first, mass_softmax, mass_topk);
   return hipGetLastError();
 }
 

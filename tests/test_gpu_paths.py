@@ -67,6 +67,18 @@ def test_routing_mass_edges(sw, hidden, m, k, tokens, eligible):
     assert np.all(np.abs(mt - o_mt) <= 2 * GAP_TOL * o_mt + 2.0 ** -22 * (o_mt + 2.0) + n_near)
 
 
+# one array for both masses takes the sum of what two would
+
+def test_routing_mass_into_one_array(sw):
+    cfg, L, D = small_layer(256, 96, 4, 32, 200, seed=33)
+    two = sw.sw_moe_routing_mass(D["x"], D["wr"], 4)
+    one = torch.zeros(96, device="cuda")
+    for _ in range(3):
+        one.zero_()
+        sw.sw_moe_routing_mass(D["x"], D["wr"], 4, mass=(one, one))
+        assert torch.equal(one, two[0] + two[1])
+
+
 # --------------------------------------------------------------------------
 # selection and plan: one wave a token and one plan wave up to 16 tokens and 64
 # pairs, the separate kernels past either edge; 1 to 16 experts a lane, pools
