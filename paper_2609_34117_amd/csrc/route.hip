@@ -599,6 +599,115 @@ __global__ __launch_bounds__(64 * kFusedMaxTokens) void route_select_dispatch_ke
               perm, active, n_active);
 }
 
+// The same for up to 32 tokens over a small pool, beyond the 64 pairs of one
+// plan wave: a row of 16 lanes selects a token (four tokens a wave, 512 threads)
+// and the block then builds the plan.  A lane holds four times the experts of
+// the wave form's, so this pays while they are few (with logits, against the
+// top-k and dispatch kernels): 32 tokens, top-4 over 32 experts 8.0 and 8.7 us,
+// over 64 8.5 and 8.9 us, top-8 over 64 9.6 and 9.7 us; over 128 the separate
+// kernels are ahead (9.3 against 10.8 us, top-4).
+constexpr int kRowFusedMaxPool = 64;  // of the experts selected from
+constexpr int kRowFusedTokens = 32, kRowFusedMaxK = 16;
+constexpr int kRowFusedThreads = 16 * kRowFusedTokens;
+
+// Reductions inside one 16-lane row (quad swaps, then the half-row and row
+// mirrors): every lane of the row ends with the row's result.
+template <typename Op>
+__device__ __forceinline__ uint32_t row_reduce_u32(uint32_t v, uint32_t identity, Op op) {
+  v = op(v, dpp_mov<dpp::kXor1>(identity, v));
+  v = op(v, dpp_mov<dpp::kXor2>(identity, v));
+  v = op(v, dpp_mov<dpp::kHalfMirror>(identity, v));
+  return op(v, dpp_mov<dpp::kMirror>(identity, v));
+}
+
+// select_topk for one token a row, lane r of it holding the keys of experts
+// q * 16 + r.  The largest key is a row maximum, the smallest expert holding
+// it a row minimum.  The softmax sum pairs the row's lanes as the first four
+// steps of the wave's sum do (whose others only add +0), so the gates are the
+// same bits.
+template <int KPL>
+__device__ __forceinline__ Selection select_row(uint32_t (&key)[KPL], const int (&eid)[KPL], int k,
+                                                int r) {
+  Selection s{-1, 0.f, 0.f, 0.f};
+  float z_first = 0.f, zk = 0.f, zk1 = 0.f;
+  bool complete = true, have_next = false;
+  for (int j = 0; j <= k; ++j) {
+    uint32_t lm = key[0];
+#pragma unroll
+    for (int q = 1; q < KPL; ++q) lm = umax(lm, key[q]);
+    const uint32_t best = row_reduce_u32(lm, 0u, umax);
+    const bool found = best != 0;  // uniform over the row
+    const float ze = f32_from_order_key(best);
+    if (j == k) {
+      zk1 = ze;
+      have_next = found;
+      break;
+    }
+    uint32_t cand = 0xffffffffu;
+#pragma unroll
+    for (int q = KPL - 1; q >= 0; --q) cand = key[q] == best ? (uint32_t)eid[q] : cand;
+    const int e = (int)row_reduce_u32(cand, 0xffffffffu,
+                                      [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+    if (!found) complete = false;
+    if (found) {
+      if (j == 0) z_first = ze;
+      if (r == j) {
+        s.id = e;
+        s.z = ze;
+      }
+      if (j == k - 1) zk = ze;
+#pragma unroll
+      for (int q = 0; q < KPL; ++q)
+        if (eid[q] == e) key[q] = 0u;
+    }
+  }
+  const float ex = r < k && s.id >= 0 ? expf(s.z - z_first) : 0.f;
+  const float sum = __uint_as_float(row_reduce_u32(
+      __float_as_uint(ex), 0u, [](uint32_t a, uint32_t b) {
+        return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+      }));
+  s.gate = s.id >= 0 ? ex / sum : 0.f;
+  s.gap = !complete ? __builtin_nanf("") : (have_next ? zk - zk1 : __builtin_inff());
+  return s;
+}
+
+template <int KPL>
+__global__ __launch_bounds__(kRowFusedThreads) void route_select_dispatch_rows_kernel(
+    const float* __restrict__ part, int KS, const float* __restrict__ bias,
+    const uint8_t* __restrict__ keep_mask, int T, Cols c, int* __restrict__ topk_ids,
+    float* __restrict__ topk_w, float* __restrict__ gap, int* __restrict__ counts,
+    int* __restrict__ offsets, int* __restrict__ perm, int* __restrict__ active,
+    int* __restrict__ n_active) {
+  constexpr int kWaves = kRowFusedThreads / kWave;
+  __shared__ int ids_s[kRowFusedTokens * kRowFusedMaxK];
+  __shared__ int cursor[kFusedMaxPool];
+  __shared__ int wave_base[kWaves * kFusedMaxPool];
+  __shared__ uint8_t wave_cnt[kWaves * kFusedMaxPool];
+  __shared__ uint32_t scan_scratch[34];
+  __shared__ int bad;
+  const int t = threadIdx.x >> 4, r = threadIdx.x & 15;
+  const int kout = c.k + c.S;
+  if ((threadIdx.x >> 6) * 4 < T) {  // wave-uniform
+    int eid[KPL];
+#pragma unroll
+    for (int q = 0; q < KPL; ++q) eid[q] = q * 16 + r;
+    const LogitParts<KPL> l = load_logits<KPL>(part, KS, T, c, t, eid);
+    const LaneExperts<KPL> x = load_experts<KPL>(c, eid, bias, keep_mask);
+    uint32_t key[KPL];
+    Routed o;
+    o.sgate = c.S > 0 ? shared_gate(l.gate, KS) : 0.f;
+    logit_keys<KPL>(l, x, KS, bias != nullptr, key);
+    o.s = select_row<KPL>(key, eid, c.k, r);
+    if (t < T) {
+      store_selection(o, t, T, c, r, topk_ids, topk_w, gap);
+      if (r < kout) ids_s[t * kout + r] = slot_id(o.s, c, r, t, T);
+    }
+  }
+  __syncthreads();
+  const DispatchLds lds{cursor, wave_base, wave_cnt, scan_scratch, &bad};
+  dispatch_block(ids_s, T * kout, c.plan_m(), lds, counts, offsets, perm, active, n_active);
+}
+
 // Split of the router contraction for T tokens and m experts: KW waves per
 // block, KS slices of H (blocks per output tile).  Few tiles (decode): 4
 // waves and up to 4 slices of H, so that about 256 blocks share the router
@@ -873,9 +982,15 @@ hipError_t launch_route_select(const uint16_t* x, int T, const float* wr, const 
   return route_cols(x, T, wr, bias, keep_mask, H, c, topk_ids, topk_w, gap, workspace, stream);
 }
 
-bool fused_route_dispatch_supported(int T, int m, int k, int S, int R) {
-  return T > 0 && T <= kFusedMaxTokens && m + R * S <= kFusedMaxPool &&
-         T * (k + S) <= kFusedMaxPairs;
+// Which one-block selection + plan a batch takes: one wave a token, a row of 16
+// lanes a token, or none.
+enum class Fused { kNone, kWaves, kRows };
+
+static Fused fused_route_dispatch(int T, int m, int k, int S, int R) {
+  if (T <= 0 || m + R * S > kFusedMaxPool) return Fused::kNone;
+  if (T <= kFusedMaxTokens && T * (k + S) <= kFusedMaxPairs) return Fused::kWaves;
+  return T <= kRowFusedTokens && k + S <= kRowFusedMaxK && m <= kRowFusedMaxPool ? Fused::kRows
+                                                                                 : Fused::kNone;
 }
 
 hipError_t launch_route_dispatch(const uint16_t* x, int T, const float* wr, const float* bias,
@@ -885,7 +1000,8 @@ hipError_t launch_route_dispatch(const uint16_t* x, int T, const float* wr, cons
                                  int n_shared, int n_groups) {
   const Cols c{m, n_shared > 0 ? m + 1 : m, k, n_shared, n_shared > 0 ? n_groups : 1};
   const int kout = k + n_shared, m_plan = c.plan_m();
-  if (!fused_route_dispatch_supported(T, m, k, n_shared, c.R)) {
+  const Fused fused = fused_route_dispatch(T, m, k, n_shared, c.R);
+  if (fused == Fused::kNone) {
     if (T > 0) {
       hipError_t err = route_cols(x, T, wr, bias, keep_mask, H, c, topk_ids, topk_w, gap,
                                   workspace, stream);
@@ -898,6 +1014,20 @@ hipError_t launch_route_dispatch(const uint16_t* x, int T, const float* wr, cons
   const LogitsSplit sp = logits_split(T, H, c.ld);
   hipError_t err = launch_logits(x, T, wr, H, c.ld, part, sp, stream);
   if (err != hipSuccess) return err;
+#define SW_FR(KPL)                                                                             \
+  route_select_dispatch_rows_kernel<KPL><<<1, kRowFusedThreads, 0, stream>>>(                    \
+      part, sp.ks, bias, keep_mask, T, c, topk_ids, topk_w, gap, counts, offsets, perm, active,   \
+      n_active)
+  if (fused == Fused::kRows) {
+    if (m <= 16)
+      SW_FR(1);
+    else if (m <= 32)
+      SW_FR(2);
+    else
+      SW_FR(4);
+    return hipGetLastError();
+  }
+#undef SW_FR
   const int kpl = (m + 63) / 64;
 #define SW_FD(KPL)                                                                             \
   route_select_dispatch_kernel<KPL><<<1, 64 * T, 0, stream>>>(                                    \

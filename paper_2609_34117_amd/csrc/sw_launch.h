@@ -47,15 +47,14 @@ hipError_t launch_dispatch(const int* topk_ids, int n_pairs, int m, int* counts,
                            int* perm, int* active, int* n_active, hipStream_t stream,
                            void* workspace = nullptr);
 
-// Route, then dispatch of the selected ids; one select + dispatch block when
-// fused_route_dispatch_supported, else the separate kernels.
+// Route, then dispatch of the selected ids; one select + dispatch block for
+// small batches, else the separate kernels.
 // With n_shared > 0 the router has a last row, the shared expert's gate,
 // and every token gets n_shared more slots after its k routed ones: the
 // shared expert's parts with the sigmoid of that gate logit.  The pool
 // holds n_groups copies of the parts; token t of T uses copy
 // g = t * n_groups / T, pool ids m + g * n_shared .. + n_shared - 1, and the
 // plan covers m + n_groups * n_shared experts.
-bool fused_route_dispatch_supported(int T, int m, int k, int n_shared = 0, int n_groups = 1);
 // The routing half of launch_route_dispatch alone (logits and top-k, same
 // outputs), for a caller that builds the plan elsewhere.
 hipError_t launch_route_select(const uint16_t* x, int T, const float* wr, const float* bias,

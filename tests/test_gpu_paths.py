@@ -81,8 +81,9 @@ def test_routing_mass_into_one_array(sw):
 
 # --------------------------------------------------------------------------
 # selection and plan: one wave a token and one plan wave up to 16 tokens and 64
-# pairs, the separate kernels past either edge; 1 to 16 experts a lane, pools
-# that end inside a wave, masks and biases
+# pairs; a row of 16 lanes a token and one plan block past either edge, up to 32
+# tokens over 64 experts; else the separate kernels; 1 to 16 experts a lane,
+# pools that end inside a wave or a row, masks and biases
 
 def plan_of(ids, m):
     """(counts, offsets, perm, active) of the pairs' ids, by a stable sort."""
@@ -111,6 +112,12 @@ def check_plan(plan, ids, m):
     (128, 1, 17, False, False),   # 17 tokens
     (257, 8, 2, False, True),     # past the fused pool
     (1000, 2, 5, True, True),     # 16 experts a lane
+    (16, 1, 17, False, True),     # rows: one expert a lane, 17 tokens
+    (17, 16, 5, True, False),     # two experts a lane, 80 pairs
+    (33, 4, 32, True, True),      # four
+    (64, 16, 32, False, False),   # the largest: 512 pairs
+    (65, 4, 32, False, True),     # past the row pool
+    (64, 4, 33, True, False),     # past the row tokens
 ])
 def test_selection_and_plan_edges(sw, m, k, tokens, masked, biased):
     cfg, L, D = small_layer(512, m, k, 32, tokens, seed=41)
@@ -127,6 +134,47 @@ def test_selection_and_plan_edges(sw, m, k, tokens, masked, biased):
                                           want_logits=True)
     compare_routing(host(ids), host(w), o_ids, o_w, o_z, mask, k, g_gap=host(gap), o_gap=o_gap)
     check_plan(plan, host(ids), m)
+
+
+# the row form against route, then dispatch, bit for bit: ties, a NaN and
+# infinite logits, fewer eligible experts than k; and, with a shared expert, against
+# batches of 3 tokens, which take the wave form
+
+@pytest.mark.parametrize("m,k,tokens", [(16, 8, 32), (50, 16, 17), (64, 2, 32)])
+def test_row_selection_equals_separate_kernels(sw, m, k, tokens):
+    cfg, L, D = small_layer(512, m, k, 32, tokens, seed=43)
+    bias = np.zeros(m, np.float32)
+    bias[1], bias[3], bias[5] = np.inf, -np.inf, np.nan
+    D["wr"][7] = D["wr"][9]  # equal logits
+    few = np.zeros(m, np.uint8)
+    few[: k - 1] = 1
+    for b, mask in ((None, None), (dev(bias), None), (None, dev(few))):
+        ids, w, gap, plan = sw.sw_moe_route_dispatch(D["x"], D["wr"], k, keep_mask=mask, bias=b)
+        r_ids, r_w, r_gap = sw.sw_moe_route(D["x"], D["wr"], k, keep_mask=mask, bias=b)
+        r_plan = sw.sw_moe_dispatch(r_ids, m)
+        assert torch.equal(ids, r_ids)
+        for a, r in ((w, r_w), (gap, r_gap)):
+            assert torch.equal(a.view(torch.int32), r.view(torch.int32))
+        n = int(r_plan.n_active.item())
+        assert int(plan.n_active.item()) == n and (n < 0) == (mask is not None)
+        for name in ("counts", "offsets", "perm"):
+            assert torch.equal(getattr(plan, name), getattr(r_plan, name))
+        assert torch.equal(plan.active[: max(n, 0)], r_plan.active[: max(n, 0)])
+
+
+@pytest.mark.parametrize("m,k,n_shared,groups,tokens", [(60, 4, 2, 2, 32), (16, 14, 2, 1, 17)])
+def test_row_selection_with_shared_expert(sw, m, k, n_shared, groups, tokens):
+    cfg, L, D = small_layer(512, m + 1, k, 32, tokens, seed=44)  # the last router row: its gate
+    ids, w, gap, plan = sw.sw_moe_route_dispatch_shared(D["x"], D["wr"], k, n_shared,
+                                                        n_groups=groups)
+    pool = m + groups * n_shared
+    for t0 in range(0, tokens, 3):
+        part = sw.sw_moe_route_dispatch_shared(D["x"][t0:t0 + 3].contiguous(), D["wr"], k, n_shared)
+        assert torch.equal(ids[t0:t0 + 3, :k], part[0][:, :k])
+        assert torch.equal(w[t0:t0 + 3], part[1]) and torch.equal(gap[t0:t0 + 3], part[2])
+    g = np.arange(tokens) * groups // tokens
+    assert np.array_equal(host(ids)[:, k:], m + g[:, None] * n_shared + np.arange(n_shared))
+    check_plan(plan, host(ids), pool)
 
 
 # the one-block plan: one pair, part of a run, both block sizes at their largest
