@@ -340,21 +340,20 @@ __global__ __launch_bounds__(kBlk, 1) void gate_up_prefill_kernel(
   uint32_t q = 0;      // slot of the chunk being computed, in bytes
   int stored = 0;      // result stores of the last pass, by this wave (0: all waited for)
   const bool overlap = n >= kGuOverlap;
-  // a pass from an empty pipeline: the first one, and every one of a short K
-  auto start = [&](bool first) {
-    walk.expert_of(cur, first);
-    walk.pairs_of();
-    walk.check();
-    if (!walk.more) return;
-    load_pids(perm_r, walk, wave, lane_id, pids_s[half]);
+  // from an empty pipeline: the first pass, and every one of a short K
+  auto fill = [&]() {
     landed_barrier();
     stored = 0;
     stage_from(walk.next, pids_s[half]);
     stage_next(0, q);
     stage_next(1, next_slot(q));
   };
-  start(true);
+  walk.expert_of(cur, true);
+  walk.pairs_of();
+  walk.check();
   if (!walk.more) return;
+  load_pids(perm_r, walk, wave, lane_id, pids_s[half]);
+  fill();
   cur = walk.next;
 
   auto run_pass = [&](auto nbc) {
@@ -471,12 +470,20 @@ __global__ __launch_bounds__(kBlk, 1) void gate_up_prefill_kernel(
           else
             wait_exactly<0>();
           pass_barrier();
+          if (c == 0) walk.expert_of(cur, false);
           if (c + 3 < n) stage(nbc, c + 3, q);
         });
     }
     // (the last chunk's slot carries the results; the next pass's chunk 2
     // follows them)
-    chunk(Yes{}, [&]() { pass_barrier(); });
+    chunk(Yes{}, [&]() {
+      pass_barrier();
+      if (!overlap) {
+        walk.pairs_of();
+        walk.check();
+        if (walk.more) load_pids(perm_r, walk, wave, lane_id, pids_s[half ^ 1]);
+      }
+    });
 
     // SwiGLU of two tiles at a time, so that every lane finishes an output:
     // lanes 0-31 hold tile a's gates and lanes 32-63 its ups (likewise for
@@ -527,13 +534,9 @@ __global__ __launch_bounds__(kBlk, 1) void gate_up_prefill_kernel(
   };
   for (;;) {
     with_blocks(cur.nb, run_pass);
-    if (overlap) {
-      half ^= 1;
-    } else {
-      pass_barrier();  // (every wave is done with the pair ids and the results' slot)
-      start(false);
-    }
     if (!walk.more) break;
+    half ^= 1;
+    if (!overlap) fill();  // (past its barrier every wave is done with the results' slot)
     cur = walk.next;
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));
