@@ -548,35 +548,23 @@ __global__ __launch_bounds__(kBlk, 1) void gate_up_prefill_kernel(
 // A chunk is one MFMA step (32 columns) of the weights and of both h planes,
 // the ring four slots.  A chunk's weight and hi operands are in registers
 // before its turn; the lo plane is read in its turn, during the hi plane's
-// MFMAs (both planes a chunk ahead take more registers than there are).
+// MFMAs (both planes a chunk ahead take more registers than there are).  As in
+// gate/up a wave issues the same number of loads for every chunk of a pass:
+// waves 0-3 stage the hi plane and waves 4-7 the lo plane.
 
 constexpr int kDnSlots = 4, kDnAhead = kDnSlots - 1;
 constexpr int kDnPlane = kNT * 32;                          // words of a staged plane
 constexpr int kDnSlot = kTpu * kFrag + 2 * kDnPlane;
 constexpr int kDnW = kTpu / kWv;                            // weight loads a wave and chunk
-constexpr int kDnHLoads = (2 * kColGroups * kMaxNb + kWv - 1) / kWv;  // at most, h loads
 
-template <bool kTiled, int NB>
-__device__ __forceinline__ void dn_read(Operands<NB>& o, const uint16_t* buf, int wave, int lane) {
-  const int r = lane & 15, kg = lane >> 4;
-  const int at = (r * 4 + place(r, kg)) * 8;
-  const uint16_t* wf = buf + (wave % kRowGroups) * kTpw * kFrag + (kTiled ? lane * 8 : at);
-  const uint16_t* bf = buf + kTpu * kFrag + (wave / kRowGroups) * NB * kFrag + at;
-#pragma unroll
-  for (int t = 0; t < kTpw; ++t) o.a[t] = *reinterpret_cast<const u32x4*>(wf + t * kFrag);
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) o.b[nb] = *reinterpret_cast<const u32x4*>(bf + nb * kFrag);
+// A plane's 1 KiB fragments (two for every column block of a wave), dealt out
+// over the plane's 4 waves; an odd number of blocks repeats half a round.
+constexpr int kPlaneWaves = kWv / 2;
+__host__ __device__ constexpr int plane_loads(int nb) {
+  return (kColGroups * nb + kPlaneWaves - 1) / kPlaneWaves;
 }
-
-template <int NB>
-__device__ __forceinline__ void dn_read_lo(u32x4 (&b)[NB], const uint16_t* buf, int wave,
-                                           int lane) {
-  const int r = lane & 15, kg = lane >> 4;
-  const uint16_t* bf = buf + kTpu * kFrag + kDnPlane + (wave / kRowGroups) * NB * kFrag +
-                       (r * 4 + place(r, kg)) * 8;
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) b[nb] = *reinterpret_cast<const u32x4*>(bf + nb * kFrag);
-}
+constexpr int kMaxPlaneLoads = plane_loads(kMaxNb);
+static_assert(kColGroups == 2 && kPlaneWaves == 4, "half a round is two fragments");
 
 template <bool kTiled>
 __global__ __launch_bounds__(kBlk, 1) void down_prefill_kernel(
@@ -592,13 +580,12 @@ __global__ __launch_bounds__(kBlk, 1) void down_prefill_kernel(
   if (n_act <= 0 || n_act > m) return;
   const int lane_id = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int plane = wave / kPlaneWaves, plane_wave = wave % kPlaneWaves;
   const int tpe = H / 16;                          // tiles per expert: 16 output rows each
-  const int nchunks = I / 32;                      // a multiple of kDnSlots
+  const int n = I / 32;                            // chunks, a multiple of kDnSlots
   const uint32_t w_bytes = 2u * (uint32_t)H * (uint32_t)I;
-  const uint32_t h_bytes = 2u * (uint32_t)n_pairs * (uint32_t)I;
-  const u32x4 hi_r = rsrc_words(h_hi, h_bytes), lo_r = rsrc_words(h_lo, h_bytes);
+  const u32x4 h_r = rsrc_words(plane ? h_lo : h_hi, 2u * (uint32_t)n_pairs * (uint32_t)I);
   const u32x4 perm_r = rsrc_words(perm, 4u * (uint32_t)n_pairs);
-  const auto yr = make_rsrc(y, 4u * (uint32_t)n_pairs * (uint32_t)H);
   uint16_t* trans = trans_s + wave * kFrag;
   PassWalk walk{active, counts, offsets, m, n_pairs, n_act * ((tpe + kTpu - 1) / kTpu),
                 (tpe + kTpu - 1) / kTpu, (int)gridDim.x, unit_slot(), {}, false};
@@ -606,8 +593,7 @@ __global__ __launch_bounds__(kBlk, 1) void down_prefill_kernel(
   // what is staged (as for gate/up); the h rows are the expert's dispatch
   // slots, so they need no pair ids
   u32x4 w_r;
-  uint32_t w_off[kDnW], b_off[kDnHLoads];
-  int b_loads;  // h fragments of the pass's chunks, over the waves
+  uint32_t w_off[kDnW], h_off[kMaxPlaneLoads];
   auto stage_from = [&](const Pass& s) {
     int lane = lane_id;
     asm volatile("" : "+v"(lane));
@@ -620,41 +606,42 @@ __global__ __launch_bounds__(kBlk, 1) void down_prefill_kernel(
                         : ((uint32_t)(tile * 16 + l_row) * (uint32_t)I + (uint32_t)l_piece * 8u) * 2u;
       if (tile >= tpe) w_off[j] = kOutOfRange;
     }
-    b_loads = 2 * kColGroups * s.nb;
 #pragma unroll
-    for (int j = 0; j < kDnHLoads; ++j) {
-      const int f = wave + j * kWv;  // hi blocks, then lo blocks
-      const int b = f >= b_loads / 2 ? f - b_loads / 2 : f;
-      const int sl = s.p0 + b * 16 + l_row;
-      b_off[j] = sl < s.cnt
+    for (int j = 0; j < kMaxPlaneLoads; ++j) {
+      const int f = plane_wave + j * kPlaneWaves, blocks = kColGroups * s.nb;
+      const int sl = s.p0 + (f < blocks ? f : f - 2) * 16 + l_row;
+      h_off[j] = sl < s.cnt
                      ? ((uint32_t)(s.base + sl) * (uint32_t)I + (uint32_t)l_piece * 8u) * 2u
                      : kOutOfRange;
     }
   };
-  auto loads_of = [&](int nb) {  // this wave's loads of a chunk
-    const int f = 2 * kColGroups * nb;
-    return kDnW + (f > wave ? (f - wave + kWv - 1) / kWv : 0);
-  };
-  auto slot = [&](int q) { return ring + q * kDnSlot; };
   const uint32_t ring_at = lds_address(ring);
-  auto stage = [&](int c, int q) {  // chunk c into slot q
-    int w0 = wave;
-    asm volatile("" : "+s"(w0));
-    const uint32_t at = ring_at + (uint32_t)(q * kDnSlot * 2 + w0 * kFrag * 2);
-#pragma unroll
-    for (int j = 0; j < kDnW; ++j)
-      load_lds16<0, kTiled>(w_r, w_off[j], (uint32_t)c * (kTiled ? 1024u : 64u),
-                            at + (uint32_t)(j * kWv * kFrag * 2));
-#pragma unroll
-    for (int j = 0; j < kDnHLoads; ++j) {
-      const int f = w0 + j * kWv;
-      if (f < b_loads) {  // wave-uniform
-        const bool lo = f >= b_loads / 2;
-        const int past = lo ? kNT / 16 - b_loads / 2 : 0;  // the lo plane follows a whole hi plane
-        load_lds16<0>(lo ? lo_r : hi_r, b_off[j], (uint32_t)c * 64u,
-                      at + (uint32_t)((kTpu + past + j * kWv) * kFrag * 2));
-      }
-    }
+  constexpr uint32_t kSlotBytes = kDnSlot * 2;
+  auto next_slot = [](uint32_t q) {
+    return q + kSlotBytes == kDnSlots * kSlotBytes ? 0u : q + kSlotBytes;
+  };
+  auto slot_before = [](uint32_t q) {
+    return q == 0 ? (kDnSlots - 1) * kSlotBytes : q - kSlotBytes;
+  };
+  // chunk c of a pass with nb column blocks into the slot at byte q
+  auto stage = [&](auto nbc, int c, uint32_t q) {
+    constexpr int NB = decltype(nbc)::value;
+    const uint32_t at = ring_at + q;
+    const uint32_t wc = (uint32_t)c * (kTiled ? 1024u : 64u), hc = (uint32_t)c * 64u;
+    const uint32_t h_at = at + (uint32_t)(plane * kDnPlane * 2 + plane_wave * 1024);
+    for_each_index<plane_loads(NB)>([&](auto j) {
+      constexpr int J = decltype(j)::value;
+      constexpr bool kRepeat = (J + 1) * kPlaneWaves > kColGroups * NB;
+      const uint32_t back = kRepeat ? (uint32_t)(plane_wave & 2) * 1024u : 0u;
+      load_lds16<kTpu * kFrag * 2 + J * kPlaneWaves * 1024>(h_r, h_off[J], hc, h_at - back);
+    });
+    for_each_index<kDnW>([&](auto j) {
+      load_lds16<decltype(j)::value * kWv * 1024, kTiled>(w_r, w_off[decltype(j)::value], wc,
+                                                          at + (uint32_t)wave * 1024u);
+    });
+  };
+  auto stage_next = [&](int c, uint32_t q) {
+    with_blocks(walk.next.nb, [&](auto nbc) { stage(nbc, c, q); });
   };
 
   Pass cur{0, 0, 0, 0, 0, 0};
@@ -669,10 +656,11 @@ __global__ __launch_bounds__(kBlk, 1) void down_prefill_kernel(
   cur = walk.next;
   stage_from(cur);
 #pragma unroll
-  for (int c = 0; c < kDnAhead; ++c) stage(c, c);
+  for (int c = 0; c < kDnAhead; ++c) stage_next(c, (uint32_t)c * kSlotBytes);
 
   auto run_pass = [&](auto nbc) {
     constexpr int NB = decltype(nbc)::value;
+    constexpr int kLoads = kDnW + plane_loads(NB);  // a wave's loads of a chunk
     int lane = lane_id;
     asm volatile("" : "+v"(lane));  // (the addresses of the five widths are not kept)
     const int r = lane & 15, kg = lane >> 4;
@@ -681,76 +669,108 @@ __global__ __launch_bounds__(kBlk, 1) void down_prefill_kernel(
     for (int t = 0; t < kTpw; ++t)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) acc[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // this wave's loads of one of the pass's chunks: kLoads, or one more
-    constexpr int kHOfAll = 2 * kColGroups * NB;
-    constexpr int kLoads = kDnW + kHOfAll / kWv;
-    const bool one_more = wave < kHOfAll % kWv;
-    int n_next = 0;
-    // Waits until only the loads of kChunks chunks of this pass, and
-    // (`stores`) the last pass's result stores, are outstanding.
-    auto wait_chunks = [&](auto chunks, bool stores) {
-      constexpr int kChunks = decltype(chunks)::value;
-      if (stores && stored > 0) {
-        if (one_more)
-          wait_one_of<kChunks*(kLoads + 1) + kTpw, kTpw, kMaxNb>(kChunks * (kLoads + 1) + stored);
-        else
-          wait_one_of<kChunks * kLoads + kTpw, kTpw, kMaxNb>(kChunks * kLoads + stored);
-      } else if (one_more) {
-        wait_exactly<kChunks*(kLoads + 1)>();
-      } else {
-        wait_exactly<kChunks * kLoads>();
+    const int at = (r * 4 + place(r, kg)) * 16;  // operand places in a slot (bytes)
+    const int w_at = (wave % kRowGroups) * kTpw * kFrag * 2 + (kTiled ? lane * 16 : at);
+    const int h_at = (kTpu + (wave / kRowGroups) * NB) * kFrag * 2 + at;
+    auto read = [&](Operands<NB>& o, uint32_t slot) {
+      const char* wb = reinterpret_cast<const char*>(ring) + (slot + (uint32_t)w_at);
+      const char* hb = reinterpret_cast<const char*>(ring) + (slot + (uint32_t)h_at);
+#pragma unroll
+      for (int t = 0; t < kTpw; ++t) o.a[t] = *reinterpret_cast<const u32x4*>(wb + t * kFrag * 2);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        o.b[nb] = *reinterpret_cast<const u32x4*>(hb + nb * kFrag * 2);
+    };
+    uint32_t q = 0;  // slot of the chunk being computed, in bytes
+    // One chunk: `before` ends with the barrier past which the next chunk has
+    // landed and the slot before this one is free, and stages into that slot.
+    auto chunk = [&](const Operands<NB>& o, Operands<NB>& ahead, auto last, auto&& before) {
+      before();
+      u32x4 lo[NB];
+      const char* lb = reinterpret_cast<const char*>(ring) + (q + (uint32_t)h_at + kDnPlane * 2);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) lo[nb] = *reinterpret_cast<const u32x4*>(lb + nb * kFrag * 2);
+      q = next_slot(q);
+      if constexpr (!decltype(last)::value) read(ahead, q);
+      __builtin_amdgcn_sched_barrier(0);  // on their way during the MFMAs
+      chunk_mfmas<NB>(o.a, o.b, acc);
+      chunk_mfmas<NB>(o.a, lo, acc);
+    };
+    using No = std::false_type;
+    using Yes = std::true_type;
+    Operands<NB> o0, o1;
+    // Chunk 0 landed: after its loads came those of two more chunks, then the
+    // last pass's stores.
+    wait_one_of<2 * kLoads, kTpw, kMaxNb + 1>(2 * kLoads + stored);
+    pass_barrier();
+    read(o0, q);
+    // Chunk c + 1 has landed when only chunk c + 2's loads (for c < 2 also the
+    // stores before or between them) are outstanding.  The next pass is looked
+    // up in chunks 0 and 1, or at once in a pass of four chunks, whose chunk 1
+    // already stages the next pass's first; its pair ids are used in its own
+    // epilogue, many chunks later.
+    const bool short_pass = n == kDnSlots;
+    auto look_up = [&]() {
+      walk.pairs_of();
+      walk.check();
+      if (walk.more) load_pids(perm_r, walk, wave, lane_id, pids_s[half ^ 1]);
+    };
+    auto turn_over = [&]() {  // three chunks before the end
+      if (walk.more) {
+        stage_from(walk.next);
+        stage_next(0, slot_before(q));
       }
     };
-    Operands<NB> ops[2];
-    // chunk 0 landed: after its loads came those of two more chunks, then the
-    // last pass's stores
-    wait_chunks(std::integral_constant<int, kDnAhead - 1>{}, true);
-    pass_barrier();
-    dn_read<kTiled, NB>(ops[0], slot(0), wave, lane);
-    for (int c0 = 0; c0 < nchunks; c0 += kDnSlots) {
-#pragma unroll
-      for (int d = 0; d < kDnSlots; ++d) {
-        const int c = c0 + d;
-        // Chunk c + 1 landed: after its loads came chunk c + 2's (or the next
-        // pass's first; with no next pass none), and for c < 2 the stores.
-        if (d < 2 || c + kDnAhead <= nchunks)
-          wait_chunks(std::integral_constant<int, kDnAhead - 2>{}, d < kDnAhead - 1 && c0 == 0);
-        else if (c + 1 < nchunks)
-          wait_one_of<0, 1, kDnW + kDnHLoads + 1>(n_next);
-        // past the barrier chunk c - 1's slot is free
-        pass_barrier();
-        // the next pass, in two steps (at once if this one is short)
-        if (c0 == 0) {
-          const bool short_pass = nchunks <= kDnSlots;
-          if (d == 0) {
-            walk.expert_of(cur, false);
-          }
-          if ((d == 0 && short_pass) || (d == 1 && !short_pass)) {
-            walk.pairs_of();
-            walk.check();
-            // (used in the next pass's epilogue, many chunks later)
-            if (walk.more) load_pids(perm_r, walk, wave, lane_id, pids_s[half ^ 1]);
-          }
-        }
-        // the chunk three later, of this pass or the next
-        if (d == kDnSlots - kDnAhead && c + kDnAhead == nchunks && walk.more) {
-          stage_from(walk.next);
-          n_next = loads_of(walk.next.nb);
-        }
-        if (c + kDnAhead < nchunks || walk.more)
-          stage(c + kDnAhead - (c + kDnAhead < nchunks ? 0 : nchunks), (d + kDnAhead) % kDnSlots);
-        u32x4 lo[NB];
-        dn_read_lo<NB>(lo, slot(d), wave, lane);
-        // (past the last chunk: bytes that nothing uses)
-        dn_read<kTiled, NB>(ops[(d + 1) & 1], slot((d + 1) % kDnSlots), wave, lane);
-        __builtin_amdgcn_sched_barrier(0);  // on their way during the MFMAs
-        chunk_mfmas<NB>(ops[d & 1].a, ops[d & 1].b, acc);
-        chunk_mfmas<NB>(ops[d & 1].a, lo, acc);
+    chunk(o0, o1, No{}, [&]() {
+      wait_one_of<kLoads, kTpw, kMaxNb + 1>(kLoads + stored);
+      pass_barrier();
+      walk.expert_of(cur, false);
+      if (short_pass) look_up();
+      stage(nbc, 3, slot_before(q));
+    });
+    chunk(o1, o0, No{}, [&]() {
+      wait_one_of<kLoads, kTpw, kMaxNb + 1>(kLoads + stored);
+      pass_barrier();
+      if (short_pass) {
+        turn_over();
+      } else {
+        look_up();
+        stage(nbc, 4, slot_before(q));
       }
+    });
+    if (!short_pass) {
+      auto middle = [&](int c) {
+        wait_exactly<kLoads>();
+        pass_barrier();
+        stage(nbc, c + 3, slot_before(q));
+      };
+      for (int c = 2; c + 4 < n; c += 2) {
+        chunk(o0, o1, No{}, [&]() { middle(c); });
+        chunk(o1, o0, No{}, [&]() { middle(c + 1); });
+      }
+      chunk(o0, o1, No{}, [&]() { middle(n - 4); });
+      chunk(o1, o0, No{}, [&]() {
+        wait_exactly<kLoads>();
+        pass_barrier();
+        turn_over();
+      });
     }
+    chunk(o0, o1, No{}, [&]() {
+      if (walk.more)
+        wait_one_of<kDnW + 1, 1, kMaxPlaneLoads>(kDnW + plane_loads(walk.next.nb));
+      else
+        wait_exactly<0>();
+      pass_barrier();
+      if (walk.more) stage_next(1, slot_before(q));
+    });
+    chunk(o1, o0, Yes{}, [&]() {
+      pass_barrier();
+      if (walk.more) stage_next(2, slot_before(q));
+    });
 
     // y: lane (r, kg) holds rows 4 kg .. + 3 of a tile for token r of a column
     // block; they pass through the wave's own LDS as gate/up's results do
+    const auto yr = make_rsrc(y, 4u * (uint32_t)n_pairs * (uint32_t)H);
     const int l_row = lane >> 2, l_piece = place(l_row, lane & 3);
     const int tile0 = cur.grp * kTpu + (wave % kRowGroups) * kTpw;
     const int blk0 = (wave / kRowGroups) * NB;
@@ -780,6 +800,180 @@ __global__ __launch_bounds__(kBlk, 1) void down_prefill_kernel(
     half ^= 1;
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));
+}
+
+// ---------------------------------------------------------------------------
+// down projection of tiled weights with long rows: weights through registers
+//
+// A wave owns two row tiles and computes every column block of a pass; its
+// weights go from memory into its registers, 2 KiB of a tile a chunk of 64
+// columns, one chunk ahead, so no wave waits for another's; only h goes through
+// LDS, two chunks of both planes.  A pass begins with an empty pipeline, which a
+// pass of the ring above does not: the fewer chunks a pass has, the more that
+// counts.  Against the ring, H 2048, 4 slots a token: I 512, 256 experts, 48 /
+// 96 / 150 tokens each: 122 / 160 / 267 us here, 120 / 151 / 244 there; I 768,
+// 128 experts: 90 / 117 / 160 here, 96 / 121 / 178 there; I 1024, 60 experts:
+// 55 / 70 / 108 here, 53 / 77 / 113 there.  Row-major weights, whose 64-byte
+// pieces cost the address path four times as much on the way into registers,
+// take the ring at every I (I 768: 110 / 138 / 192 us so, 108 / 130 / 184 there).
+
+constexpr int kRingDownMaxI = 512;              // tiled rows up to which the ring is used
+constexpr int kRgTpw = 2;                       // row tiles a wave
+constexpr int kRgCols = 64, kRgSteps = kRgCols / 32;
+constexpr int kRgRows = 8;                      // staged rows per 1 KiB load of a wave
+static_assert(kWv * kRgTpw == kTpu, "one unit size");
+
+// A pass of NBK column blocks (those past the pass's tokens multiply zero
+// rows).  The ring slots are distinct restrict pointers: the compiler then
+// knows that the loads into one do not write the one being read.
+template <int NBK>
+__device__ __forceinline__ void down_regs_pass(__amdgpu_buffer_rsrc_t w,
+                                               __amdgpu_buffer_rsrc_t hi_r,
+                                               __amdgpu_buffer_rsrc_t lo_r, int tile0, int tpe,
+                                               const int* __restrict__ perm, int n_pairs,
+                                               uint16_t* __restrict__ slot0,
+                                               uint16_t* __restrict__ slot1,
+                                               __amdgpu_buffer_rsrc_t yr, int base, int p0,
+                                               int cnt, int H, int I, int lane, int wave) {
+  constexpr int kHalf = NBK * 16 / kRgRows;     // a plane's loads a chunk, over the waves
+  static_assert(2 * kHalf % kWv == 0, "whole rounds of loads");
+  constexpr int kLoads = 2 * kHalf / kWv, kWLoads = kRgTpw * kRgSteps;
+  const int r = lane & 15, kg = lane >> 4, n = I / kRgCols;  // n chunks, an even number
+  auto swizzle = [](int row) { return (row & 7) ^ ((row >> 3) & 1); };
+  // the y row of each of this lane's output columns; loaded now, before the
+  // staging loads that the waits count
+  int pid[NBK];
+#pragma unroll
+  for (int nb = 0; nb < NBK; ++nb) {
+    const int sl = p0 + nb * 16 + r;
+    const int p = sl < cnt ? perm[base + sl] : -1;
+    pid[nb] = p >= 0 && p < n_pairs ? p : -1;
+  }
+  uint32_t off[kLoads];  // this lane's piece of each load in chunk 0
+#pragma unroll
+  for (int j = 0; j < kLoads; ++j) {
+    const int f = wave + j * kWv, row = (f < kHalf ? f : f - kHalf) * kRgRows + (lane >> 3);
+    const int piece = (lane & 7) ^ swizzle(row);
+    off[j] = p0 + row < cnt ? ((uint32_t)(base + p0 + row) * I + (uint32_t)piece * 8u) * 2u
+                            : kOutOfRange;
+  }
+  auto stage = [&](int c, uint16_t* buf) {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+      const int f = wave + j * kWv;  // hi rows, then lo rows
+      const bool lo = f >= kHalf;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          lo ? lo_r : hi_r,
+          (__attribute__((address_space(3))) void*)(buf + ((lo ? kNT : 0) +
+                                                           (lo ? f - kHalf : f) * kRgRows) * kRgCols),
+          16, off[j] + (uint32_t)c * kRgCols * 2u, 0, 0, 0);
+    }
+  };
+  auto issue = [&](int c, u32x4 (&A)[kRgTpw][kRgSteps]) {
+#pragma unroll
+    for (int t = 0; t < kRgTpw; ++t) {
+      const uint32_t at = (uint32_t)(tile0 + t) * 32u * I + (uint32_t)lane * 16u;
+      const bool ok = c < n && tile0 + t < tpe;
+#pragma unroll
+      for (int st = 0; st < kRgSteps; ++st)
+        A[t][st] = buf_ld128_stream(w, ok ? at + (uint32_t)(c * kRgSteps + st) * 1024u : kOutOfRange);
+    }
+  };
+  int h_at[kRgSteps];
+#pragma unroll
+  for (int st = 0; st < kRgSteps; ++st) h_at[st] = ((st * 4 + kg) ^ swizzle(r)) * 8;
+
+  stage(0, slot0);
+  __builtin_amdgcn_sched_barrier(0);  // the load order the waits below count on
+  u32x4 A[2][kRgTpw][kRgSteps];
+  issue(0, A[0]);
+  __builtin_amdgcn_sched_barrier(0);
+  f32x4 acc[kRgTpw][NBK];
+#pragma unroll
+  for (int t = 0; t < kRgTpw; ++t)
+#pragma unroll
+    for (int nb = 0; nb < NBK; ++nb) acc[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < n; c0 += 2) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      // chunk c0 + d of h landed (its weights, issued after it, need not have),
+      // and every wave is done with the other slot
+      __builtin_amdgcn_s_waitcnt(vmcnt_at_most_lds_done(kWLoads));
+      __builtin_amdgcn_s_barrier();
+      stage(c0 + d + 1, d ? slot0 : slot1);  // (past the end: rows that nothing reads)
+      __builtin_amdgcn_sched_barrier(0);
+      issue(c0 + d + 1, A[d ^ 1]);
+      __builtin_amdgcn_sched_barrier(0);  // loads ahead of the chunk's MFMAs
+      const uint16_t* buf = d ? slot1 : slot0;
+#pragma unroll
+      for (int st = 0; st < kRgSteps; ++st) {
+#pragma unroll
+        for (int nb = 0; nb < NBK; ++nb) {
+          const uint16_t* row = buf + (nb * 16 + r) * kRgCols + h_at[st];
+          const u32x4 bh = *reinterpret_cast<const u32x4*>(row);
+          const u32x4 bl = *reinterpret_cast<const u32x4*>(row + kNT * kRgCols);
+#pragma unroll
+          for (int t = 0; t < kRgTpw; ++t) {
+            acc[t][nb] = mfma_16x16x32(A[d][t][st], bh, acc[t][nb]);
+            acc[t][nb] = mfma_16x16x32(A[d][t][st], bl, acc[t][nb]);
+          }
+        }
+      }
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_at_most(0));  // the loads past the end landed
+
+  // lane (r, kg) holds output rows tile * 16 + 4 kg .. + 3 of pair pid[nb]
+#pragma unroll
+  for (int t = 0; t < kRgTpw; ++t) {
+#pragma unroll
+    for (int nb = 0; nb < NBK; ++nb) {
+      const uint32_t at = tile0 + t < tpe && pid[nb] >= 0
+                              ? ((uint32_t)pid[nb] * H + (uint32_t)((tile0 + t) * 16 + kg * 4)) * 4u
+                              : kOutOfRange;
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[t][nb]), yr, at, 0, 0);
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBlk, 1) void down_prefill_regs_kernel(
+    const uint16_t* __restrict__ h_hi, const uint16_t* __restrict__ h_lo,
+    const uint16_t* __restrict__ w2, const int* __restrict__ counts,
+    const int* __restrict__ offsets, const int* __restrict__ perm,
+    const int* __restrict__ active, const int* __restrict__ n_active, float* __restrict__ y, int H,
+    int I, int m, int n_pairs) {
+  __shared__ __attribute__((aligned(1024))) uint16_t slot0[2 * kNT * kRgCols];
+  __shared__ __attribute__((aligned(1024))) uint16_t slot1[2 * kNT * kRgCols];
+  const int n_act = *n_active;
+  if (n_act <= 0 || n_act > m) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int tpe = H / 16, gpe = (tpe + kTpu - 1) / kTpu;
+  const uint32_t h_bytes = 2u * (uint32_t)n_pairs * (uint32_t)I;
+  const auto hi_r = make_rsrc(h_hi, h_bytes), lo_r = make_rsrc(h_lo, h_bytes);
+  const auto yr = make_rsrc(y, 4u * (uint32_t)n_pairs * (uint32_t)H);
+  for (int u = unit_slot(); u < n_act * gpe; u += gridDim.x) {
+    const int a = u / gpe, e = active[a];
+    if (e < 0 || e >= m) continue;
+    const int cnt = counts[e], base = offsets[e];
+    if (cnt <= 0 || base < 0 || cnt > n_pairs - base) continue;
+    const auto w = make_rsrc(w2 + (size_t)e * H * I, 2u * (uint32_t)H * (uint32_t)I);
+    const int tile0 = (u - a * gpe) * kTpu + wave * kRgTpw;
+    for (int p0 = 0; p0 < cnt; p0 += kNT) {
+      const int blocks = (min(kNT, cnt - p0) + 15) >> 4;
+      __syncthreads();  // the previous pass's reads of the ring are done
+      auto pass = [&](auto nbk) {
+        down_regs_pass<decltype(nbk)::value>(w, hi_r, lo_r, tile0, tpe, perm, n_pairs, slot0,
+                                             slot1, yr, base, p0, cnt, H, I, lane, wave);
+      };
+      if (blocks <= 4)
+        pass(std::integral_constant<int, 4>{});
+      else if (blocks <= 8)
+        pass(std::integral_constant<int, 8>{});
+      else
+        pass(std::integral_constant<int, kNT / 16>{});
+    }
+  }
 }
 
 int prefill_grid() {
@@ -824,7 +1018,10 @@ hipError_t launch_down_prefill(int T, const uint16_t* w2, bool tiled, const int*
                                const int* n_active, int H, int I, int m, int k,
                                const uint16_t* h_hi, const uint16_t* h_lo, float* y,
                                hipStream_t stream) {
-  if (tiled)
+  if (tiled && I > kRingDownMaxI)
+    down_prefill_regs_kernel<<<prefill_grid(), kBlk, 0, stream>>>(
+        h_hi, h_lo, w2, counts, offsets, perm, active, n_active, y, H, I, m, T * k);
+  else if (tiled)
     down_prefill_kernel<true><<<prefill_grid(), kBlk, 0, stream>>>(
         h_hi, h_lo, w2, counts, offsets, perm, active, n_active, y, H, I, m, T * k);
   else

@@ -219,12 +219,14 @@ def test_wide_logits_edges(sw, hidden, m, tokens, k):
 # to look up the next pass (H 384), the first that does (H 512), longer ones;
 # row tiles that end inside a unit (H 128, 384; I 128, 384); more units than
 # blocks (300 experts), experts of several passes, from 1 to 10 column blocks;
-# units that start inside the row (H 2048, row-major)
+# units that start inside the row (H 2048, row-major); tiled rows past the ring
+# of the down projection (I 640, 768)
 
 @pytest.mark.parametrize("tiled", [False, True])
 @pytest.mark.parametrize("hidden,inter,m,k,tokens", [
     (128, 128, 16, 1, 256), (384, 256, 16, 4, 700), (512, 128, 300, 8, 640),
     (512, 384, 16, 8, 330), (1152, 256, 24, 4, 450), (2048, 384, 16, 2, 300),
+    (384, 640, 16, 8, 330), (1152, 768, 24, 4, 700),
 ])
 def test_prefill_kernel_edges(sw, hidden, inter, m, k, tokens, tiled):
     cfg, L, D = small_layer(hidden, m, k, inter, tokens, seed=53)

@@ -84,16 +84,23 @@ def too_close(asm):
 
 
 def compilers_own_m0(asm):
-    """Instructions outside inline assembly that name M0."""
-    found, inline = [], False
-    for line in asm.splitlines():
-        text = line.strip()
-        if text in (";APP", ";;#ASMSTART"):
-            inline = True
-        elif text in (";NO_APP", ";;#ASMEND"):
-            inline = False
-        elif not inline and re.search(r"\bm0\b", text.split(";")[0]):
-            found.append(text)
+    """In functions with LDS loads in inline assembly, the instructions outside
+    it that name M0."""
+    found = []
+    for function in asm.split("; -- Begin function"):
+        inline, own, loads = False, [], False
+        for line in function.splitlines():
+            text = line.strip()
+            if text == ";;#ASMSTART":
+                inline = True
+            elif text == ";;#ASMEND":
+                inline = False
+            elif inline:
+                loads = loads or text.endswith(" lds")
+            elif re.search(r"\bm0\b", text.split(";")[0]):
+                own.append(text)
+        if loads:
+            found += own
     return found
 
 
@@ -112,8 +119,10 @@ def test_scanner_sees_the_distance():
     assert not too_close(short.replace("s_nop 0", "s_mov_b32 s43, 0"))  # another writer since
     over_branch = "L:\ns_nop 2\n" + lds + "v_readfirstlane_b32 s40, v1\ns_branch L\n"
     assert [d for *_, d in too_close(over_branch)] == [4]
-    assert not compilers_own_m0(";;#ASMSTART\ns_mov_b32 m0, s5\n;;#ASMEND\ns_nop 0 ; m0\n")
-    assert len(compilers_own_m0(";;#ASMSTART\n;;#ASMEND\n\ts_mov_b32 m0, s5\n")) == 1
+    load = ";;#ASMSTART\ns_mov_b32 m0, s5\n" + lds + ";;#ASMEND\ns_nop 0 ; m0\n"
+    own = "\ts_mov_b32 m0, s5\n"
+    assert not compilers_own_m0(load + "; -- Begin function f\n" + own)
+    assert len(compilers_own_m0(own + "; -- Begin function f\n" + load + own)) == 1
 
 
 @pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs hipcc")
