@@ -75,9 +75,15 @@ typedef struct {
 const char* sw_status_str(int status);
 
 /* Kernel families of the expert FFN calls, as sw_moe_forward_kernels
- * reports them.  Every family computes the same products; the split-K
- * family adds a tile's K slices in a different order than the others, so
- * its results can differ from theirs in the last bits. */
+ * reports them.  Every family computes the same products, but not every one
+ * adds them over K in the same order: the wave and the prefill kernels add in
+ * ascending K, the split-K and the generic ones in slices, and the prefill
+ * gate/up of row-major weights with H a multiple of 2048 (rows a multiple of
+ * 4 KiB apart) from a column inside the row on.  So the results of one token
+ * can differ in the last bits between calls of different families -- another
+ * batch size, a compacted pool instead of a mask, another n_groups -- and, in
+ * that last case, between the two layouts; within a family and layout they are
+ * the same bits. */
 typedef enum {
   SW_KERNELS_NONE = 0,    /* T == 0: nothing is launched */
   SW_KERNELS_PREFILL = 1, /* >= 16 pairs per expert, pool >= 16, H and I multiples of 128 */
@@ -208,7 +214,8 @@ size_t sw_moe_route_shared_workspace_bytes(const sw_moe_dims* d, int32_t n_token
  * columns of its down projection) then adds
  *   sigmoid(wr[m] . x_t) * W2s (silu(W1s x_t) * W3s x_t)
  * to each token's output on the routed experts' launches, bit for bit the
- * same for every n_groups.  n_groups trades weight bytes for pass shape:
+ * same for every n_groups that takes the same kernel family (see
+ * sw_kernel_family).  n_groups trades weight bytes for pass shape:
  * each copy's parts receive one pair per token of their group, so with
  * groups of at most 32 tokens every part is a one-pass expert, where one
  * copy of a batch of more than 32 tokens gives parts with every token

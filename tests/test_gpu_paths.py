@@ -242,11 +242,81 @@ def test_prefill_kernel_edges(sw, hidden, inter, m, k, tokens, tiled):
     g_ids, g_w = host(g["topk_ids"]), host(g["topk_w"])
     compare_out(host(g["out"]), oracle.forward(L["x"], L["w13"], L["w2"], g_ids, g_w))
     # the wave kernels accumulate every output over K in the same order (the
-    # split-K ones, which small batches of the deeper layers take, do not)
+    # split-K ones, which small batches of the deeper layers take, do not; row-major
+    # rows of H 2048: test_prefill_order_of_sums)
     same_order = tiled or hidden % 2048 != 0
     if same_order and sw.sw_moe_forward_kernels(d, 16, layout) == ("wave", "wave"):
         small = _layer_in_batches(sw, D, k, 16, layout, bias=dev(bias))
         assert torch.equal(g["out"], small)
+
+
+# --------------------------------------------------------------------------
+# where the families' order of summation over K shows (sw_kernel_family): rows a
+# multiple of 4 KiB apart make the row-major prefill gate/up start inside the row.
+# h is rounded to two bf16 planes, 2^-17 of it at most, whatever the order; the sums
+# before it differ by less (64 roundings of 2^-25 of about the sum, at random), so
+# two orders give outputs within 2^-16 of each other in the 2-norm.  Everything
+# else here, and all of it in the tiled layout, is the same bits.
+
+def _rel(a, b):
+    return float(torch.linalg.vector_norm((a - b).double()) / torch.linalg.vector_norm(b.double()))
+
+
+@pytest.mark.parametrize("tiled", [False, True])
+@pytest.mark.parametrize("hidden", [1920, 2048])
+def test_prefill_order_of_sums(sw, hidden, tiled):
+    inter, m, k, tokens = 512, 96, 8, 96  # 768 pairs: 16 an expert of half the pool, 8 of all
+    cfg, L, D = small_layer(hidden, m, k, inter, tokens, seed=61)
+    g = sw.sw_moe_prune_compact(D["importance"], m // 2, k, w13=D["w13"], w2=D["w2"], wr=D["wr"])
+    layout, pack = sw.ROW_MAJOR, lambda w13, w2: (w13, w2)
+    if tiled:
+        layout, pack = sw.TILED, sw.sw_moe_pack_experts
+    full = dict(D, w13=pack(D["w13"], D["w2"])[0], w2=pack(D["w13"], D["w2"])[1])
+    comp = dict(x=D["x"], wr=g["wr"], w13=pack(g["w13"], g["w2"])[0],
+                w2=pack(g["w13"], g["w2"])[1])
+    families = [sw.sw_moe_forward_kernels(sw.dims(hidden, inter, e, k), t, layout)
+                for e, t in ((m, tokens), (m // 2, tokens), (m // 2, 32))]
+    assert families == [("wave", "wave"), ("prefill", "prefill"), ("wave", "wave")]
+
+    def layer(d, **kw):
+        return sw.moe_layer(d["x"], d["wr"], d["w13"], d["w2"], k, layout=layout, **kw)
+
+    whole = layer(comp)
+    others = {
+        "masked": layer(full, keep_mask=g["keep_mask"])["out"],
+        "batches": _layer_in_batches(sw, comp, k, 32, layout),
+        "layouts": sw.moe_layer(D["x"], g["wr"], *sw.sw_moe_pack_experts(g["w13"], g["w2"]), k,
+                                layout=sw.TILED)["out"],
+    }
+    assert torch.equal(layer(comp)["out"], whole["out"])
+    for name, out in others.items():
+        if tiled or hidden % 2048 != 0:
+            assert torch.equal(out, whole["out"]), name
+        else:
+            assert _rel(out, whole["out"]) <= 2.0 ** -16, name
+    g_ids, g_w = host(whole["topk_ids"]), host(whole["topk_w"])
+    compare_out(host(whole["out"]), oracle.forward(L["x"], host(g["w13"]), host(g["w2"]), g_ids, g_w))
+
+
+@pytest.mark.parametrize("hidden", [1920, 2048])
+def test_token_groups_across_families(sw, hidden):
+    # 640 pairs: the pool of 24 experts and one copy of the shared expert's two
+    # parts is prefill-sized (16 pairs an expert), with nine copies it is not
+    inter, m, k, S, tokens = 512, 24, 8, 2, 64
+    cfg, L, D = small_layer(hidden, m + 1 + S, k, inter, tokens, seed=67)
+    wr = D["wr"][: m + 1].contiguous()
+    out, families = [], []
+    for groups in (1, 9):
+        w13 = torch.cat([D["w13"][:m]] + [D["w13"][m + 1:]] * groups)
+        w2 = torch.cat([D["w2"][:m]] + [D["w2"][m + 1:]] * groups)
+        families.append(sw.sw_moe_forward_kernels(
+            sw.dims(hidden, inter, m + groups * S, k + S), tokens, sw.ROW_MAJOR))
+        out.append(sw.sw_moe_layer(D["x"], wr, k, w13, w2, n_shared=S, n_groups=groups)[4])
+    assert families == [("prefill", "prefill"), ("wave", "wave")]
+    if hidden % 2048 != 0:
+        assert torch.equal(out[0], out[1])
+    else:
+        assert _rel(out[0], out[1]) <= 2.0 ** -16
 
 
 # --------------------------------------------------------------------------
