@@ -404,21 +404,24 @@ template <bool kTiled>
 __device__ __forceinline__ void gu_issue(const GuWave& g, int j, int c, u32x4 (&A)[kKC]) {
   const int tile = g.seg_lo + g.wave + j * kWv;
   const int ib = tile - g.a * g.tpe;
-  uint32_t row, stride;
-  if (kTiled) {
-    row = (uint32_t)ib * 32u * g.H + (uint32_t)g.lane * 16u;
-    stride = 1024u;
+  const bool live = tile < g.seg_hi;
+  if constexpr (kTiled) {
+    const uint32_t row = (uint32_t)ib * 32u * g.H + (uint32_t)g.lane * 16u;
+#pragma unroll
+    for (int s = 0; s < kKC; ++s) {
+      const int step = c * kKC + s;
+      const uint32_t off = (live && step < g.nsteps) ? row + (uint32_t)step * 1024u : kOutOfRange;
+      A[s] = buf_ld128_stream(g.w, off);
+    }
   } else {
     const int wrow = g.r < 8 ? ib * 8 + g.r : g.I + ib * 8 + (g.r - 8);
-    row = (uint32_t)wrow * g.H * 2u + g.kg * 16u;
-    stride = 64u;
-  }
-  const bool live = tile < g.seg_hi;
+    const uint32_t row = (uint32_t)wrow * g.H * 2u + g.kg * 16u;
 #pragma unroll
-  for (int s = 0; s < kKC; ++s) {
-    const int step = c * kKC + s;
-    const uint32_t off = (live && step < g.nsteps) ? row + (uint32_t)step * stride : kOutOfRange;
-    A[s] = kTiled ? buf_ld128_stream(g.w, off) : buf_ld128(g.w, off);
+    for (int s = 0; s < kKC; ++s) {
+      const int step = c * kKC + s;
+      const uint32_t off = (live && step < g.nsteps) ? row + (uint32_t)step * 64u : kOutOfRange;
+      A[s] = buf_ld128(g.w, off);
+    }
   }
 }
 
