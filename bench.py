@@ -78,16 +78,16 @@ PAPER_CONTEXT = {
 # HBM traffic of one gate_up launch on the default workload (batch 64, 50%
 # pruned, tiled pool), from two rocprofv3 --pmc passes of
 # `bench.py --no-cpu-baseline --steps 20 --warmup 5` (summary in
-# profiles/gate_up_wave_decode_b64_hbm_traffic.md): FETCH_SIZE 197810.72 KiB x
-# 1.99982 (the ratio of bytes copied to FETCH_SIZE over 12 plain device copies
-# of 192-768 MiB) + WRITE_SIZE 1569.78 KiB x 1.0 (WRITE_SIZE of the copies is
+# profiles/gate_up_wave_decode_b64_hbm_traffic.md): FETCH_SIZE 197812.5 KiB x
+# 1.99969 (the ratio of bytes copied to FETCH_SIZE over 12 plain device copies
+# of 192-768 MiB) + WRITE_SIZE 1574.3 KiB x 1.0 (WRITE_SIZE of the copies is
 # exact).  The figure holds while the gate/up kernel's sources hash as below.
 KERNEL_SOURCES = ("paper_2609_34117_amd/csrc/expert_stream.hip",
                   "paper_2609_34117_amd/csrc/sw_device.h",
                   "paper_2609_34117_amd/csrc/dispatch_block.h")
-GATE_UP_TRAFFIC = dict(sources_sha256="56176f85a277c412facb401dc52d2926856fa035a8939e2f9dc4d6d6233febb6",
+GATE_UP_TRAFFIC = dict(sources_sha256="7bd866506db27b29cf6284c5c833e44083a7b42ebe2e3ef9df82a93d32840989",
                        workload=("decode_b64", 64, 0.5, "tiled"),
-                       bytes_per_launch=int(round((197810.72 * 1.99982 + 1569.78) * 1024)))
+                       bytes_per_launch=int(round((197812.5 * 1.99969 + 1574.3) * 1024)))
 
 
 def parse():

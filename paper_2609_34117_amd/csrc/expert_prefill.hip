@@ -22,23 +22,22 @@
 //     pass are computed, and its results stored, while the first chunks of
 //     the next (its expert, pairs and rows looked up a few chunks earlier)
 //     are already on their way.
+// (The down projection of long tiled rows is a kernel of another form, below.)
 // Each output accumulates over K in the same order as the decode kernels,
 // except where the rows of a row-major w13 are a multiple of 4 KiB apart.
 //
 // What bounds it (4096 tokens, 256 experts, H 2048, I 512, top-8: 137 GFLOP of
-// gate/up products, 137 of down's over two planes, 1.6 and 0.8 GB of weights):
-// gate/up with its loads alone runs 179 us for the weights (6 TB/s) and 192
-// with the activations, its LDS reads and MFMAs alone about 180, so that
-// neither can hide the other's last part; down's loads alone are 96 us, the
-// rest MFMAs (the planes double them), LDS reads and 268 MB of results.
+// gate/up products, 137 of down's over two planes, 1.07 and 0.54 GB of weights):
+// memory.  With the MFMAs and operand reads left out gate/up takes 210 of its
+// 228 us (1.28 GB at 6.1 TB/s) and down 198 of its 204 (0.61 GB read, 0.27
+// written); with the loads left out 134 and 101.  1531 row-major tokens over 128
+// experts of I 768: 167 of 170 and 128 of 129.
 // Before, the weights came through registers one 64-column chunk ahead, two
 // row tiles a wave (an LDS operand fed two MFMAs), each pass began with an
-// empty pipeline and results were stored a token per lane.  Before -> now:
-// gate/up 249 -> 235 us, down 227 -> 203..213, the reduction that reads its
-// results 54 -> 48 (full lines written); the step 525 -> 491 us.  1531 row-major
-// tokens over 128 experts, I 768: gate/up 210 -> 170, down 137 -> 138 (tiled
-// 148 and 124).  256 tokens over 64 experts: unchanged
-// within 1 us (88 and 55).
+// empty pipeline and results were stored a token per lane.  Before -> now, kernel
+// traces at 4096 tokens: gate/up 234 -> 225 us, down 208 -> 200, the reduction
+// that reads its results 52 -> 48 (whole lines written: down wrote 297 MB for
+// 268).  1531 row-major tokens: gate/up 206 -> 170, down 137 -> 129.
 #include <type_traits>
 
 #include "sw_device.h"
@@ -550,7 +549,11 @@ __global__ __launch_bounds__(kBlk, 1) void gate_up_prefill_kernel(
 // before its turn; the lo plane is read in its turn, during the hi plane's
 // MFMAs (both planes a chunk ahead take more registers than there are).  As in
 // gate/up a wave issues the same number of loads for every chunk of a pass:
-// waves 0-3 stage the hi plane and waves 4-7 the lo plane.
+// waves 0-3 stage the hi plane and waves 4-7 the lo plane.  (With the fragments
+// dealt over all waves and the waits chosen at run time, 4 to 9% slower for 150
+// and more row-major tokens an expert.  With 64 columns a chunk in two slots:
+// 0 to 9% faster from 128 tokens an expert on, but up to 12% slower at 48 and
+// fewer, where a chunk's loads have nothing in flight behind them.)
 
 constexpr int kDnSlots = 4, kDnAhead = kDnSlots - 1;
 constexpr int kDnPlane = kNT * 32;                          // words of a staged plane

@@ -509,7 +509,8 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
 // one token over 256 experts and 9.7 us for 8, against 10.4 us for the top-k
 // and dispatch kernels at 8.  Beyond, one block would serialise selections and
 // plan (two tokens a wave and a block-wide plan took 9.5 against 8.8 us at 20
-// tokens over 32 experts, and 12.8 against 10.8 us over 256).
+// tokens over 32 experts, and 12.8 against 10.8 us over 256); over small pools
+// the row form below takes such batches.
 constexpr int kFusedMaxPool = 256;
 constexpr int kFusedMaxTokens = 16;
 constexpr int kFusedMaxPairs = 64;
@@ -711,9 +712,15 @@ __global__ __launch_bounds__(kRowFusedThreads) void route_select_dispatch_rows_k
 // Split of the router contraction for T tokens and m experts: KW waves per
 // block, KS slices of H (blocks per output tile).  Few tiles (decode): 4
 // waves and up to 4 slices of H, so that about 256 blocks share the router
-// bytes; many tiles (prefill): route_logits_wide_kernel's 64 x 64 tiles over
-// slices of at least 8 chunks of H (2 at H = 2048), or, when H is not a
-// whole number of chunks, 2-wave 16 x 16 tiles and no split.
+// bytes; many tiles (prefill): route_logits_wide_kernel's tiles of 128 tokens x
+// 64 experts over slices of at least 8 units of 128 columns (2 slices at H =
+// 2048), or, when H is not a whole number of units, 2-wave 16 x 16 tiles and no
+// split.  At 1024 tiles the wide form fills a quarter of the chip (64 blocks at
+// 1024 tokens x 256 experts, H 2048) and is ahead all the same: logits and top-k
+// 18.6 us, 22.2 with the 64-token register tiles it replaced, and it stayed ahead
+// of those at every size measured up to 32,768 tokens, but for pools of at most
+// 24 experts right past 16,384 tokens, where two slices leave a last wave of two
+// blocks (33.9 against 32.6 us at 8 experts).
 struct LogitsSplit {
   int kw, ks;
   bool wide;  // route_logits_wide_kernel
@@ -779,7 +786,7 @@ void launch_topk(const float* part, int KS, const float* bias, const uint8_t* ke
 // order that depends on nothing but the shape.  (One thread per expert
 // walking all tokens, as this was, is one chain of T dependent exponentials
 // on 256 threads of the chip: 1672 us of a 1681 us call at 4096 tokens over
-// 256 experts, H 2048.  Now the whole call takes 44 us, 27 of them the logits,
+// 256 experts, H 2048.  Now the whole call takes 37 us, 19 of them the logits,
 // and needs no dispatch plan.)
 
 constexpr int kMassWaves = 8;        // waves per block of the first kernel

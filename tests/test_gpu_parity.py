@@ -612,16 +612,21 @@ def test_dispatch_plan_block_size_boundaries(sw, tokens, m, k):
     np.testing.assert_array_equal(host(plan.active)[:n_active], active)
 
 
-@pytest.mark.parametrize("n_experts,top_k", [(64, 8), (128, 8), (256, 16), (40, 3)])
-def test_topk_row_and_wave_forms_agree_bit_for_bit(sw, n_experts, top_k):
-    # 63 tokens take one token per 16-lane row, 64 one token per wave; the
-    # logits of the shared tokens are the same, so ids, gates and gaps must be
+@pytest.mark.parametrize("n_experts,top_k,tokens", [
+    (64, 8, 32), (40, 3, 32),     # the row form (a token per 16-lane row, the plan by the block)
+    (128, 8, 8), (256, 16, 4),    # the wave form with the plan (64 pairs)
+    (128, 8, 33), (256, 16, 63),  # the top-k kernel itself on part of the batch
+])
+def test_selection_forms_agree_bit_for_bit(sw, n_experts, top_k, tokens):
+    # sw_moe_route of 64 tokens takes the top-k kernel (a token per wave); the
+    # first tokens' logits are the same in a smaller batch, so whatever form
+    # selects there, ids, gates and gaps must be
     cfg, L, D = small_layer(2048, n_experts, top_k, 32, 64, seed=13)
     ids64, w64, gap64 = sw.sw_moe_route(D["x"], D["wr"], top_k)
-    ids63, w63, gap63 = sw.sw_moe_route(D["x"][:63].contiguous(), D["wr"], top_k)
-    assert torch.equal(ids64[:63], ids63)
-    assert torch.equal(w64[:63], w63)
-    assert torch.equal(gap64[:63], gap63)
+    ids, w, gap, _ = sw.sw_moe_route_dispatch(D["x"][:tokens].contiguous(), D["wr"], top_k)
+    assert torch.equal(ids64[:tokens], ids)
+    assert torch.equal(w64[:tokens], w)
+    assert torch.equal(gap64[:tokens], gap)
 
 
 def test_exact_logit_ties_break_to_smaller_id(sw):
@@ -766,26 +771,26 @@ def _assert_same_route_dispatch(a, b):
 
 @pytest.mark.parametrize("hidden,n_experts,top_k,tokens,masked,biased", [
     (256, 16, 2, 8, False, False),        # tiny shape, one logit slice
-    (2048, 64, 8, 32, False, False),      # largest fused batch, compacted 64-expert pool
-    (2048, 128, 8, 21, True, False),      # full pool under a 50% mask, ragged last wave
+    (2048, 64, 8, 32, False, False),      # the row form's largest batch and pool
+    (2048, 128, 8, 21, True, False),      # a 50% mask; separate kernels, ragged last block
     (2048, 256, 8, 1, False, True),       # one token, 256 experts, with bias
-    (2048, 64, 8, 4, True, False),        # 4 tokens: the one-wave route + plan, 32 pairs
-    (2048, 128, 16, 4, False, True),      # 64 pairs: the one-wave path at its limit
-    (512, 256, 1, 3, False, False),       # k = 1 on the one-wave path
-    (256, 16, 2, 5, False, False),        # 5 tokens: the 512-thread block again
-    (2048, 256, 16, 32, True, True),      # largest fused k
-    (2048, 128, 8, 33, True, False),      # 33 tokens: row-form multi-block top-k, then dispatch
-    (2048, 128, 8, 64, False, False),     # 64 tokens: wave-form top-k, then dispatch
+    (2048, 64, 8, 4, True, False),        # 4 tokens: a wave each, one wave's plan of 32 pairs
+    (2048, 128, 16, 4, False, True),      # 64 pairs: the one-wave plan at its limit
+    (512, 256, 1, 3, False, False),       # k = 1 on the one-wave plan
+    (256, 16, 2, 5, False, False),        # 5 tokens, 10 pairs
+    (2048, 256, 16, 32, True, True),      # k = 16 over 256 experts: separate kernels
+    (2048, 128, 8, 33, True, False),      # 33 tokens: top-k, then dispatch
+    (2048, 128, 8, 64, False, False),     # 64 tokens: the same
     (2048, 64, 16, 64, True, True),       # 1024 pairs, k = 16
     (2048, 256, 8, 256, False, True),     # 2048 pairs: the largest one-block dispatch
-    (2048, 512, 8, 256, False, False),    # 2048 pairs over 512 experts, wave top-k (8 per lane)
+    (2048, 512, 8, 256, False, False),    # 2048 pairs over 512 experts (8 per lane)
     (1024, 200, 16, 100, True, False),    # k = 16, ragged last top-k block
     (2048, 256, 8, 600, False, False),    # 4800 pairs: chunked multi-block dispatch
     (2048, 256, 8, 4096, True, False),    # prefill: wide logit tiles, 32 dispatch chunks
     (1536, 100, 6, 700, False, True),     # wide logit tiles with ragged token and expert tiles
-    (512, 300, 8, 40, False, False),      # m > 256: separate kernels, wave top-k
-    (1024, 600, 4, 40, False, False),     # m > 512: 10 experts per lane of the wave top-k
-    (256, 64, 17, 20, False, False),      # k > 16: separate kernels, wave top-k
+    (512, 300, 8, 40, False, False),      # m > 256
+    (1024, 600, 4, 40, False, False),     # m > 512: 10 experts per lane
+    (256, 64, 17, 20, False, False),      # k > 16: separate kernels over a small pool
     (520, 12, 4, 70, True, False),        # ragged H
 ])
 def test_route_dispatch_equals_route_then_dispatch(sw, hidden, n_experts, top_k, tokens, masked,
@@ -817,9 +822,9 @@ def test_route_dispatch_in_band_errors_and_empty_batch(sw):
     b = sw.sw_moe_route_dispatch(D["x"], D["wr"], 3, keep_mask=dev(mask))
     _assert_same_route_dispatch(a, b)
     assert int(b[3].n_active.item()) == -1      # the missing third choice flags the batch
-    # the same flag after the multi-block top-k, row form (40 tokens) and
-    # wave form (70 tokens, 210 pairs)
-    for tokens in (40, 70):
+    # the same flag from the row form (30 tokens, 90 pairs) and after the
+    # separate top-k (70 tokens)
+    for tokens in (30, 70):
         cfg, L, D = small_layer(64, 8, 3, 32, tokens, seed=5)
         a = _route_then_dispatch(sw, D["x"], D["wr"], 3, 8, keep_mask=dev(mask))
         b = sw.sw_moe_route_dispatch(D["x"], D["wr"], 3, keep_mask=dev(mask))
@@ -1008,16 +1013,16 @@ def _folded_layer(sw, L, w13s, w2s, gate, top_k, n_shared, mask, tiled, n_groups
 
 
 @pytest.mark.parametrize("hidden,n_experts,top_k,inter,tokens,n_shared,masked,tiled,groups", [
-    (2048, 64, 8, 512, 64, 2, False, True, 1),    # batch 64: wave-form top-k, then dispatch;
+    (2048, 64, 8, 512, 64, 2, False, True, 1),    # batch 64: top-k, then dispatch;
                                                   # parts with every token (two passes)
     (2048, 64, 8, 512, 64, 2, False, True, 2),    # the same in two groups of 32 tokens
-    (2048, 128, 8, 512, 1, 2, True, False, 1),    # one token: the one-wave route + plan
-    (2048, 128, 8, 512, 3, 2, True, False, 3),    # 3 groups of one token: the one-wave path
-    (2048, 64, 8, 768, 17, 1, False, False, 1),   # 17 tokens: the 512-thread block, one part
-    (2048, 64, 8, 768, 17, 1, False, True, 2),    # the 512-thread block, groups of 8 and 9
-    (2048, 256, 8, 512, 100, 2, False, True, 1),  # 100 tokens: wave-form top-k, then dispatch
+    (2048, 128, 8, 512, 1, 2, True, False, 1),    # one token: selection + plan in one block
+    (2048, 128, 8, 512, 3, 2, True, False, 3),    # 3 groups of one token: the same
+    (2048, 64, 8, 768, 17, 1, False, False, 1),   # 17 tokens: the row form, one part
+    (2048, 64, 8, 768, 17, 1, False, True, 2),    # the row form, groups of 8 and 9
+    (2048, 256, 8, 512, 100, 2, False, True, 1),  # 100 tokens: top-k, then dispatch
     (2048, 256, 8, 512, 100, 2, False, True, 4),  # four groups of 25 tokens
-    (1024, 200, 14, 256, 40, 2, True, False, 3),  # k + parts = 16: the row form at its limit
+    (1024, 200, 14, 256, 40, 2, True, False, 3),  # k + parts = 16, 3 groups of 13 and 14
     (2048, 96, 6, 512, 200, 4, False, False, 1),  # 4 parts: 200-token parts over gate/up passes
     (2048, 128, 8, 512, 64, 2, False, True, 4),   # the shared-expert benchmark's shape: 128
                                                   # experts, 2 parts in 4 groups of 16 tokens
